@@ -83,14 +83,6 @@ constexpr int kDirectPrio = MEMFINE_DIRECT_PRIO;
 #define MEMFINE_CARRY_STEP 1
 #endif
 constexpr bool kCarryStep = MEMFINE_CARRY_STEP;
-// Weight gradients adding into dW: 1 = the epilogue loads the old values and
-// adds them to the tile's sum; 0 = the accumulators start from them, loaded
-// before the tile's first MFMA (that wait also waits for the previous tile's
-// stores, which the next tile's first K steps otherwise hide).
-#ifndef MEMFINE_DW_ADD_IN_EPILOGUE
-#define MEMFINE_DW_ADD_IN_EPILOGUE 1
-#endif
-constexpr bool kDwAddInEpilogue = MEMFINE_DW_ADD_IN_EPILOGUE;
 // s_waitcnt lgkmcnt(0): this wave's LDS reads have returned
 __device__ __forceinline__ void wait_lgkm0() {
   __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
@@ -216,15 +208,6 @@ __device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, char* lds, 
 __device__ __forceinline__ u32x4_t load_reg16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
 }
-// 16-byte store; an offset past the resource's range is dropped by the
-// hardware, so the instruction issues whatever the lane's element is
-__device__ __forceinline__ void store_f32x4(__amdgpu_buffer_rsrc_t r, uint32_t voff, const float (&v)[4]) {
-  f32x4_t x;
-#pragma clang loop unroll(full)
-  for (int c = 0; c < 4; ++c) x[c] = v[c];
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), r, voff, 0, 0);
-}
-
 // 4 floats as 4 bf16 (8 bytes)
 __device__ __forceinline__ u32x2_t pack4(const float (&f)[4]) {
   u32x2_t x;
@@ -426,11 +409,23 @@ template <class C> __device__ __forceinline__ void zero_acc(Accum<C>& acc) {
       for (int q = 0; q < 16; ++q) acc.v[i][j][q] = 0.f;
 }
 
+// Operand order of the product (P::kRowsInRegs).  false: the MFMA gets the B
+// fragment first, so a lane of the accumulator block holds one output row and
+// runs of consecutive columns; true: A first, a lane holds one output column
+// and the block's rows lie in its registers.  Each element is the same sum
+// either way.
+template <typename T, bool kRowsInRegs>
+__device__ __forceinline__ void mma_block(const typename Mma<T>::Frag& a,
+                                          const typename Mma<T>::Frag& b, f32x16_t& c) {
+  if constexpr (kRowsInRegs) Mma<T>::mma(a, b, c);
+  else Mma<T>::mma(b, a, c);
+}
+
 // One K tile: the operand fragments of K step kk+1 are read from LDS while
 // the MFMAs of step kk run (two fragment register sets); scheduling
 // barriers interleave the LDS reads with the MFMAs so that neither waits
 // on the other.
-template <typename T, class C, class OA, class OB>
+template <typename T, class C, class OA, class OB, bool kRowsInRegs = false>
 __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C>& acc, int wm,
                                          int wn, int lane) {
   constexpr int KS = C::KB / (int)sizeof(T) / Mma<T>::kKStep;
@@ -457,7 +452,8 @@ __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C
 #pragma clang loop unroll(full)
     for (int i = 0; i < C::MB; ++i)
 #pragma clang loop unroll(full)
-      for (int j = 0; j < C::NB; ++j) Mma<T>::mma(b[cu][j], a[cu][i], acc.v[i][j]);
+      for (int j = 0; j < C::NB; ++j)
+        mma_block<T, kRowsInRegs>(a[cu][i], b[cu][j], acc.v[i][j]);
   }
   if constexpr (kSchedHints) {
     // DS reads of step 0, then per step: MFMAs of step kk interleaved with the
@@ -491,7 +487,7 @@ __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C
 template <typename T, class C> struct FragSets {
   typename Mma<T>::Frag a[2][C::MB], b[2][C::NB];
 };
-template <typename T, class C, class OA, class OB, bool kCarry>
+template <typename T, class C, class OA, class OB, bool kCarry, bool kRowsInRegs>
 __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, Accum<C>& acc, int wm,
                                                int wn, int lane, FragSets<T, C>& f) {
   constexpr int KS = C::KB / (int)sizeof(T) / Mma<T>::kKStep;
@@ -508,7 +504,8 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
 #pragma clang loop unroll(full)
     for (int i = 0; i < C::MB; ++i)
 #pragma clang loop unroll(full)
-      for (int j = 0; j < C::NB; ++j) Mma<T>::mma(f.b[1][j], f.a[1][i], acc.v[i][j]);
+      for (int j = 0; j < C::NB; ++j)
+        mma_block<T, kRowsInRegs>(f.a[1][i], f.b[1][j], acc.v[i][j]);
   }
 #pragma clang loop unroll(full)
   for (int kk = 0; kk + 1 < KS; ++kk) {
@@ -521,7 +518,8 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
 #pragma clang loop unroll(full)
     for (int i = 0; i < C::MB; ++i)
 #pragma clang loop unroll(full)
-      for (int j = 0; j < C::NB; ++j) Mma<T>::mma(f.b[cu][j], f.a[cu][i], acc.v[i][j]);
+      for (int j = 0; j < C::NB; ++j)
+        mma_block<T, kRowsInRegs>(f.a[cu][i], f.b[cu][j], acc.v[i][j]);
   }
   if constexpr (kSchedHints) {
     // the carried MFMAs interleaved with step 0's reads, then per step the
@@ -549,15 +547,15 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
   }
   if constexpr (kPrio > 0) __builtin_amdgcn_s_setprio(0);
 }
-template <typename T, class C>
+template <typename T, class C, bool kRowsInRegs>
 __device__ __forceinline__ void mma_flush(Accum<C>& acc, const FragSets<T, C>& f) {
 #pragma clang loop unroll(full)
   for (int i = 0; i < C::MB; ++i)
 #pragma clang loop unroll(full)
-    for (int j = 0; j < C::NB; ++j) Mma<T>::mma(f.b[1][j], f.a[1][i], acc.v[i][j]);
+    for (int j = 0; j < C::NB; ++j) mma_block<T, kRowsInRegs>(f.a[1][i], f.b[1][j], acc.v[i][j]);
 }
 
-// Accumulator layout.  The MFMA is given the B fragment as its first operand,
+// Accumulator layout (kRowsInRegs false).  The MFMA is given the B fragment first,
 // so block (mb, nb) holds the transposed product: element q of a lane sits at
 // tile row acc_row(wm, mb, lane) and tile column acc_col(wn, nb, q / 4, lane)
 // + q % 4.  Each lane thus owns one output row and four runs of four
@@ -1302,7 +1300,6 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
   __device__ __forceinline__ bool acc_of(const Tile& t) const {
     return kAcc < 0 ? t.acc != 0 : kAcc == 1;
   }
-  static constexpr bool kAccLoads = kAcc != 0 && !kDwAddInEpilogue;
   __host__ __device__ static int tiles_per_expert(const GemmArgs& g) {
     return ((M(g) + C::BM - 1) / C::BM) * ((N(g) + C::BN - 1) / C::BN);
   }
@@ -1434,34 +1431,11 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
 #pragma clang loop unroll(full)
     for (int d = 0; d < D; ++d) load_tokens(d, wave, lane, tok[d]);
   }
-  // Accumulating into dW: by default the accumulators start at zero and the
-  // epilogue adds the old dW values (dW = old + this launch's sum).  Built
-  // with MEMFINE_DW_ADD_IN_EPILOGUE=0 they start from the old values instead,
-  // loaded with the tile's first operand copies.  Rows past the tile and runs
-  // past N load from clamped in-range addresses; those accumulators are
-  // never stored.
-  __device__ __forceinline__ void init_acc(const GemmArgs& g, const Tile& t, Accum<C>& acc, int wm,
-                                          int wn, int lane) const {
-    if (kDwAddInEpilogue || !acc_of(t)) {
-      zero_acc(acc);
-      return;
-    }
-    const float* dW = (kFC1 ? g.dW1 : g.dW2) + (int64_t)t.e * M(g) * N(g);
-    const int Nn = N(g);
-#pragma clang loop unroll(full)
-    for (int mb = 0; mb < C::MB; ++mb) {
-      const int r = acc_row<C>(wm, mb, lane);
-      const float* o = dW + (int64_t)(t.m0 + (r < t.mrows ? r : 0)) * Nn;
-#pragma clang loop unroll(full)
-      for (int nb = 0; nb < C::NB; ++nb)
-#pragma clang loop unroll(full)
-        for (int gq = 0; gq < 4; ++gq) {
-          const int n = t.n0 + acc_col<C>(wn, nb, gq, lane);
-          const f32x4_t v = Vec4<float>::load_raw(o + (n < Nn ? n : t.n0));
-#pragma clang loop unroll(full)
-          for (int c = 0; c < 4; ++c) acc.v[mb][nb][gq * 4 + c] = v[c];
-        }
-    }
+  // Adding into dW: the accumulators start at zero and the epilogue adds the
+  // old values (dW = old + this launch's sum).
+  __device__ __forceinline__ void init_acc(const GemmArgs&, const Tile&, Accum<C>& acc, int, int,
+                                          int) const {
+    zero_acc(acc);
   }
   __device__ __forceinline__ void commit(char* As, char* Bs, int wave, int lane) const {
     A.commit(As, wave, lane);
@@ -1499,51 +1473,76 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
       for (int i = 0; i < IG; ++i) tok[d][i] = tok[d + 1][i];
     load_tokens(kt + D, wave, lane, tok[D - 1]);  // D tiles ahead
   }
+  // The block's rows lie in registers (mma_block), so that one 4-byte store
+  // (load) instruction covers 128 contiguous bytes of each of two rows.  The
+  // epilogue is bound by the requests that reach the L2 and, when adding, by
+  // the latency of the old values: with a lane holding 4 columns of a row, a
+  // 16-byte store touched 32 rows in 32-byte pieces, four times the requests,
+  // and each block of 32 rows waited for its own loads; now the loads run two
+  // blocks ahead.  FC1 wgrad at 16384 slots, 32 experts, h 7168, F 2048:
+  // adding 2.36 -> 1.87 ms, writing 1.62 -> 1.46 ms (3.76 GB of dW1 read and
+  // written at the copy rate: 1.45 ms); at 131072 slots 7.60 -> 7.21 ms.
+  static constexpr bool kRowsInRegs = true;
   // Vector-memory stores epilogue() issues: every one, whatever the tile's
   // extent (elements outside it get an offset past the range).  When it adds
   // into dW it also loads the old values and waits for them, so the loads
   // are retired, with everything issued before them, when it returns.
-  static constexpr int kEpiStores = C::MB * C::NB * 4;
+  static constexpr int kEpiStores = C::MB * C::NB * 16;
   __device__ __forceinline__ void epilogue(const GemmArgs& g, const Tile& t, const Accum<C>& acc,
                                            int wm, int wn, int lane, char* slab) const {
-    const int Nn = N(g);  // % 64 == 0: a run of 4 columns is all in or all out
+    const int Nn = N(g);  // % 64 == 0 and M % 32 == 0: a 32 x 32 block is all in or all out
     const uint32_t rowb = (uint32_t)Nn * sizeof(float);
     // the tile is the workgroup's: its fields are uniform, which the compiler
     // cannot always prove (the resource must sit in scalar registers)
     const int e = __builtin_amdgcn_readfirstlane(t.e);
     const int m0 = __builtin_amdgcn_readfirstlane(t.m0);
     const int mrows = __builtin_amdgcn_readfirstlane(t.mrows);
+    const int n0 = __builtin_amdgcn_readfirstlane(t.n0);
     const __amdgpu_buffer_rsrc_t rs =
         make_rsrc((kFC1 ? g.dW1 : g.dW2) + (int64_t)e * M(g) * Nn + (int64_t)m0 * Nn,
                   (int64_t)mrows * rowb);
-    const bool add = kDwAddInEpilogue && acc_of(t);
+    const bool add = acc_of(t);
+    constexpr int U = C::MB * C::NB, D = U < 3 ? U : 3;  // blocks; blocks of old values in flight
+    // Lane l of block u: column l % 32, rows 8 gq + 4 (l / 32) + c.  The lane's
+    // offset is fixed, the row goes in the scalar offset.
+    const uint32_t lane_off = (uint32_t)(lane & 31) * 4 + (uint32_t)(lane >> 5) * 4 * rowb;
+    auto voff = [&](int u) {
+      const int mb = u / C::NB, nb = u % C::NB;
+      const int col = n0 + wn * C::WTN + nb * 32;
+      return wm * C::WTM + mb * 32 < mrows && col < Nn ? lane_off + (uint32_t)col * 4 : kOOB;
+    };
+    auto soff = [&](int u, int q) {
+      return (uint32_t)(wm * C::WTM + (u / C::NB) * 32 + 8 * (q >> 2) + (q & 3)) * rowb;
+    };
+    float old[D][16];
+    auto fetch = [&](int u) {
+      const uint32_t vo = voff(u);
 #pragma clang loop unroll(full)
-    for (int mb = 0; mb < C::MB; ++mb) {
-      const int r = acc_row<C>(wm, mb, lane);
-      const uint32_t ro = r < mrows ? (uint32_t)r * rowb : kOOB;
-      f32x4_t old[C::NB][4];
-      if (add) {
+      for (int q = 0; q < 16; ++q)
+        old[u % D][q] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, soff(u, q), 0));
+    };
+    auto put = [&](int u, bool added) {
+      const uint32_t vo = voff(u);
 #pragma clang loop unroll(full)
-        for (int nb = 0; nb < C::NB; ++nb)
-#pragma clang loop unroll(full)
-          for (int gq = 0; gq < 4; ++gq) {
-            const int n = t.n0 + acc_col<C>(wn, nb, gq, lane);
-            old[nb][gq] = __builtin_bit_cast(
-                f32x4_t, load_reg16(rs, n < Nn ? ro + (uint32_t)n * sizeof(float) : kOOB, 0));
-          }
+      for (int q = 0; q < 16; ++q) {
+        float v = acc.v[u / C::NB][u % C::NB][q];
+        if (added) v += old[u % D][q];
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, vo, soff(u, q),
+                                              0);
       }
+    };
+    if (add) {
 #pragma clang loop unroll(full)
-      for (int nb = 0; nb < C::NB; ++nb)
+      for (int u = 0; u + 1 < D; ++u) fetch(u);
 #pragma clang loop unroll(full)
-        for (int gq = 0; gq < 4; ++gq) {
-          const int n = t.n0 + acc_col<C>(wn, nb, gq, lane);
-          float v[4];
-          acc_run(acc.v[mb][nb], gq, v);
-          if (add)
+      for (int u = 0; u < U; ++u) {
+        if (u + D - 1 < U) fetch(u + D - 1);
+        put(u, true);
+      }
+    } else {
 #pragma clang loop unroll(full)
-            for (int c = 0; c < 4; ++c) v[c] += old[nb][gq][c];
-          store_f32x4(rs, n < Nn ? ro + (uint32_t)n * sizeof(float) : kOOB, v);
-        }
+      for (int u = 0; u < U; ++u) put(u, false);
     }
   }
 };
@@ -1564,10 +1563,10 @@ template <int N> __device__ __forceinline__ void wait_vm() {
 struct NoNext {
   __device__ __forceinline__ void operator()(char*, int, int) const {}
 };
-// Problems whose init_acc may load the accumulators (P::acc_on tells when).
-template <class P, class = void> struct AccLoads { static constexpr bool value = false; };
-template <class P> struct AccLoads<P, decltype((void)P::kAccLoads)> {
-  static constexpr bool value = P::kAccLoads;
+// Problems whose accumulators hold output rows in registers (mma_block).
+template <class P, class = void> struct RowsInRegs { static constexpr bool value = false; };
+template <class P> struct RowsInRegs<P, decltype((void)P::kRowsInRegs)> {
+  static constexpr bool value = P::kRowsInRegs;
 };
 // Problems whose epilogue leaves at most P::kEpiStores vector-memory
 // instructions in flight (its stores; loads it waits for) can take the deep
@@ -1643,12 +1642,7 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
   if (!prefetched) p.init(g, t, w, lane);
   Accum<C> acc;
   p.init_acc(g, t, acc, wm, wn, lane);
-  // Accumulators loaded from memory: wait here, once.  Left to the compiler,
-  // the waits for them land inside the K loop's multiply (its loop state
-  // merges this entry with the loop's own), where they also wait for the
-  // copies each K step has just issued.
-  if constexpr (AccLoads<P>::value)
-    if (p.acc_of(t)) wait_vm<0>();
+  constexpr bool kRows = RowsInRegs<P>::value;
   constexpr int kCopies = P::OA::I + P::OB::I;  // copy instructions per wave per K tile
   const int nk = k_tiles<T, C>(t);
   if constexpr (C::DIRECT) {
@@ -1682,19 +1676,19 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
       if constexpr (kCarryStep) {
         if (active) {
           if (kt == 0)
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, false>(cur, cur + C::BM * C::KB, acc,
-                                                                     wm, wn, lane, fr);
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, false, kRows>(
+                cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
           else
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, true>(cur, cur + C::BM * C::KB, acc,
-                                                                    wm, wn, lane, fr);
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, true, kRows>(
+                cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
         }
       } else {
         if (active)
-          mma_tile<T, C, typename P::OA, typename P::OB>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
+          mma_tile<T, C, typename P::OA, typename P::OB, kRows>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
       }
     }
     if constexpr (kCarryStep)
-      if (active && nk > 0) mma_flush<T, C>(acc, fr);
+      if (active && nk > 0) mma_flush<T, C, kRows>(acc, fr);
   } else {
     // Register-staged double buffer: the loads of tile kt + 1 are in flight
     // while tile kt is multiplied, then written to the stage that tile kt - 1
@@ -1716,15 +1710,15 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
       if constexpr (kCarryStep) {
         if (active) {
           if (kt == 0)
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, false>(cur, cur + C::BM * C::KB, acc,
-                                                                     wm, wn, lane, fr);
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, false, kRows>(
+                cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
           else
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, true>(cur, cur + C::BM * C::KB, acc,
-                                                                    wm, wn, lane, fr);
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, true, kRows>(
+                cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
         }
       } else {
         if (active)
-          mma_tile<T, C, typename P::OA, typename P::OB>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
+          mma_tile<T, C, typename P::OA, typename P::OB, kRows>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
       }
       if (more) {
         wait_vm<0>();
@@ -1732,7 +1726,7 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
       }
     }
     if constexpr (kCarryStep)
-      if (active && nk > 0) mma_flush<T, C>(acc, fr);
+      if (active && nk > 0) mma_flush<T, C, kRows>(acc, fr);
   }
   next(smem, w, lane);
   char* slab = slab_of<C, kArray>(smem, w);

@@ -1,0 +1,63 @@
+"""Kernels at the edges of their tiles and of the ranges their dispatch rules
+cover, against the fp64 oracle (tolerance: TOL of the harness, the bound on
+one output tensor's max error that the rounding of bf16 intermediates or of
+the fp32 path's sums stays below)."""
+import numpy as np
+import pytest
+
+import moe_workloads as mw
+from gpu_harness import TOL, device_case, host, log, relerr, run_bwd, run_fwd, torch
+from oracle import moe as om
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mf():
+    t = torch()
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2511_21431_amd as m
+    m.lib()
+    return m
+
+
+def _check_bwd(mf, w, seed, C, accumulate, **opts):
+    t = torch()
+    case = mw.make_case(w, seed)
+    dev = device_case(w, case)
+    ref = om.moe_bwd(case["X"], case["idx"], case["gates"], case["W1"], case["W2"],
+                     case["dY"], C)
+    dW = None
+    if accumulate:
+        gen = t.Generator(device="cuda")
+        gen.manual_seed(seed)
+        dW = [t.randn(s, generator=gen, device="cuda") for s in
+              ((w.E, 2 * w.F, w.h), (w.E, w.h, w.F))]
+        base = [x.double().cpu().numpy() for x in dW]
+    try:
+        mf.memfine_set_launch_options(**opts)
+        got = run_bwd(w, dev, C, dW=dW, accumulate=accumulate)
+    finally:
+        mf.memfine_set_launch_options()
+    if accumulate:
+        ref = dict(ref, dW1=ref["dW1"] + base[0], dW2=ref["dW2"] + base[1])
+    for key in ("dX", "dgates", "dW1", "dW2"):
+        err = relerr(host(got[key]), ref[key])
+        log(f"  {key} {err:.2e}")
+        assert err <= TOL[w.dtype], (key, err)
+
+
+# Weight-gradient epilogue: a 32 x 32 block is stored whole or not at all, so
+# every count of valid 64-row and 64-column pieces in a last tile of 256 or
+# 128, with dW overwritten, added to by a second chunk and added to throughout;
+# E = 80 fills the grid of the persistent launch with its quarter tiles.
+@pytest.mark.parametrize("h,F,E,dtype", [
+    (64, 64, 4, "bf16"), (128, 192, 3, "bf16"), (192, 64, 5, "bf16"), (320, 192, 80, "bf16"),
+    (448, 320, 2, "bf16"), (192, 320, 3, "f32"), (64, 64, 2, "f32")])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_wgrad_tile_edges(mf, h, F, E, dtype, accumulate):
+    w = mw.Workload("edge", T=321, h=h, F=F, E=E, k=2, dtype=dtype, routing="dirichlet")
+    log(f"wgrad edges h={h} F={F} E={E} {dtype} accumulate={accumulate}")
+    for opts in ({}, {"tile": mf.TILE_256}) if dtype == "bf16" else ({},):
+        _check_bwd(mf, w, 300 + h + F, 2, accumulate, **opts)
