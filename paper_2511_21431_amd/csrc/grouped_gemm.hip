@@ -48,6 +48,8 @@
 // a cold expert costs only its own ceil(rows/BM) tiles; the weight-gradient
 // GEMMs (K = the expert's rows) visit experts in descending row count, the
 // longest tiles first.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -1568,6 +1570,11 @@ template <class P, class = void> struct RowsInRegs { static constexpr bool value
 template <class P> struct RowsInRegs<P, decltype((void)P::kRowsInRegs)> {
   static constexpr bool value = P::kRowsInRegs;
 };
+// Problems whose tile columns pair gate and up rows inside a wave (FC1).
+template <class P, class = void> struct PairedColumns { static constexpr bool value = false; };
+template <class P> struct PairedColumns<P, decltype((void)P::kHalf)> {
+  static constexpr bool value = true;
+};
 // Problems whose epilogue leaves at most P::kEpiStores vector-memory
 // instructions in flight (its stores; loads it waits for) can take the deep
 // prefetch below.
@@ -1763,7 +1770,7 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
 // (K = the expert's rows) differ in cost, which the hardware's dynamic
 // dispatch balances better than a fixed stride (measured 3-8 % faster).
 template <class C, class P>
-constexpr bool kPersistent = C::DIRECT && C::S == 2 && P::kEqualTiles;
+constexpr bool kPersistent = C::DIRECT && P::kEqualTiles;
 // Weight gradients (direct copies, tile cost = the expert's rows) run
 // persistent with a tile counter when the launch provides one: each
 // workgroup takes the next tile in launch order (experts by descending row
@@ -1772,6 +1779,49 @@ constexpr bool kPersistent = C::DIRECT && C::S == 2 && P::kEqualTiles;
 // epilogue's dW stores.
 template <class C, class P>
 constexpr bool kDynamic = C::DIRECT && C::S == 2 && !P::kEqualTiles && !P::kEpilogueLoads;
+
+// Whole tiles: ids blockIdx.x, + gridDim.x, ... below n.  At the end of each
+// tile's K loop the next tile is located, its copy offsets set and its first
+// K tiles' copies issued, so that they fly while this tile's epilogue runs.
+template <typename T, class C, class P>
+__device__ __forceinline__ void run_persistent(const GemmArgs& g, char* smem, int n) {
+  const int stride = gridDim.x;
+  P p;
+  Tile t;
+  int id = blockIdx.x;
+  bool ok = false;
+  while (id < n && !(ok = p.locate(g, t, id, n))) id += stride;
+  bool pre = false;
+  while (ok) {
+    P pn;
+    Tile tn;
+    int idn = id + stride;
+    bool okn = false;
+    // every wave at the hook or past the epilogue is past its last MFMA,
+    // so its LDS reads have returned: after a barrier the stages are free
+    auto next = [&](char* sm, int w, int lane) {
+      while (idn < n && !(okn = pn.locate(g, tn, idn, n))) idn += stride;
+      if (okn) {
+        __builtin_amdgcn_s_barrier();
+        pn.init(g, tn, w, lane);
+        issue_prologue<T, C, P>(g, sm, pn, tn, w, lane);
+      }
+    };
+    if constexpr (!P::kEpilogueLoads) {
+      run_located<T, C, P>(g, smem, p, t, pre, next);   // copies fly during the epilogue
+    } else {
+      // the epilogue's own loads would wait behind earlier copies: issue
+      // the next tile's copies once the epilogue is done
+      run_located<T, C, P>(g, smem, p, t, pre);
+      next(smem, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
+    }
+    p = pn;
+    t = tn;
+    id = idn;
+    ok = okn;
+    pre = okn;
+  }
+}
 
 // A launch with a split tail.  Tiles of configuration C fill the full
 // rounds (floor(tiles / cus) * cus of them); when the last, partial round
@@ -1801,44 +1851,7 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
   const int nmain = split ? full : tiles;   // ids that run whole tiles
   const int stride = gridDim.x;
   if constexpr (kPersistent<C, P>) {
-    // Whole tiles: ids blockIdx.x, + stride, ...  At the end of each tile's
-    // K loop the next tile is located, its copy offsets set and its first K
-    // tiles' copies issued, so that they fly while this tile's epilogue runs.
-    P p;
-    Tile t;
-    int id = blockIdx.x;
-    bool ok = false;
-    while (id < nmain && !(ok = p.locate(g, t, id, nmain))) id += stride;
-    bool pre = false;
-    while (ok) {
-      P pn;
-      Tile tn;
-      int idn = id + stride;
-      bool okn = false;
-      // every wave at the hook or past the epilogue is past its last MFMA,
-      // so its LDS reads have returned: after a barrier the stages are free
-      auto next = [&](char* sm, int w, int lane) {
-        while (idn < nmain && !(okn = pn.locate(g, tn, idn, nmain))) idn += stride;
-        if (okn) {
-          __builtin_amdgcn_s_barrier();
-          pn.init(g, tn, w, lane);
-          issue_prologue<T, C, P>(g, sm, pn, tn, w, lane);
-        }
-      };
-      if constexpr (!P::kEpilogueLoads) {
-        run_located<T, C, P>(g, smem, p, t, pre, next);   // copies fly during the epilogue
-      } else {
-        // the epilogue's own loads would wait behind earlier copies: issue
-        // the next tile's copies once the epilogue is done
-        run_located<T, C, P>(g, smem, p, t, pre);
-        next(smem, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
-      }
-      p = pn;
-      t = tn;
-      id = idn;
-      ok = okn;
-      pre = okn;
-    }
+    run_persistent<T, C, P>(g, smem, nmain);
     if (split) {
       for (int q = blockIdx.x; q < 4 * rem; q += stride) {
         PQ pq;
@@ -1940,6 +1953,15 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
   }
 }
 
+// A persistent launch of one tile configuration (no split tail).
+template <typename T, class C, class P>
+__global__ __launch_bounds__(C::kThreads, C::kMinWaves)
+__attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_gemm_persistent_kernel(
+    GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) char smem[C::kLds + kSlabArea<C>];
+  run_persistent<T, C, P>(g, smem, P::total_tiles(g));
+}
+
 // The dgrad and the wgrad of one FC layer in one launch (nd + nw workgroups;
 // the two problems are independent).  Every dgrad tile reduces over the same
 // K (h or 2F); a wgrad tile reduces over its expert's rows.  Workgroups are
@@ -1976,15 +1998,21 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
   else run_tile<T, C, PW>(g, smem, lead + (int)(j - a), nw);
 }
 
-template <template <typename, class> class PT, class C>
-hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
-  const int blocks = PT<float, C>::grid(g);
+// One tile per workgroup.
+template <typename T, template <typename, class> class PT, class C>
+hipError_t launch_tiles(const GemmArgs& g, hipStream_t s) {
+  const int blocks = PT<T, C>::grid(g);
   if (blocks <= 0) return hipSuccess;
-  if (g.dtype == 0)
-    grouped_gemm_kernel<bf16_t, C, PT<bf16_t, C>><<<blocks, C::kThreads, 0, s>>>(g);
-  else
-    grouped_gemm_kernel<float, Small, PT<float, Small>><<<PT<float, Small>::grid(g), Small::kThreads,
-                                                          0, s>>>(g);
+  grouped_gemm_kernel<T, C, PT<T, C>><<<blocks, C::kThreads, 0, s>>>(g);
+  return hipGetLastError();
+}
+// As many workgroups as are resident, each walking its share of the tiles.
+template <typename T, template <typename, class> class PT, class C>
+hipError_t launch_walk(const GemmArgs& g, hipStream_t s) {
+  const int bound = PT<T, C>::grid(g);
+  if (bound <= 0) return hipSuccess;
+  grouped_gemm_persistent_kernel<T, C, PT<T, C>>
+      <<<std::min(bound, g.cus * std::max(1, C::kWgPerCu)), C::kThreads, 0, s>>>(g);
   return hipGetLastError();
 }
 
@@ -2012,6 +2040,9 @@ inline double rounds(int tiles, int per_cu) {
 
 using Big8 = Cfg<256, 256, 2, 4, 2>;        // 8 waves of 128 x 64
 using Big8R = Cfg<256, 256, 2, 4, 2, 128, 0>;  // Big8 with register-staged copies
+using Thin = Cfg<64, 128, 2, 2, 3>;         // 4 waves of 32 x 64, three stages, two per CU
+using F32N = Cfg<64, 64, 2, 2, 2>;          // fp32: 4 waves of 32 x 32, five per CU
+using F32P = Cfg<64, 128, 2, 2, 2>;         // fp32 FC1 (gate and up columns): 32 x 64, three per CU
 using Quarter8 = Cfg<128, 128, 4, 2, 2>;        // quarter tiles of Big8 (8 waves of 32 x 64)
 
 template <typename T, class C> using FC1Fwd = ProbFC1<T, C, false>;
@@ -2039,10 +2070,34 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Pick the tile shape.  The 256 x 256 tile on 8 waves (one workgroup per CU,
-// two waves per SIMD, 128 x 64 per wave) measured fastest on every workload
-// shape here, from 8k to 65k slots and C = 1..4; the 128 x 128 tile (two
-// workgroups per CU) only serves grids too small to give most CUs a tile.
+// Pick the tile shape.  Whatever is picked, an element is the same sum.
+//
+// bf16, row-grouped problems (by n / E, the rows of an average expert; the
+// host does not know the counts).  Measured at 32 experts, h 2048, F 1408,
+// Dirichlet loads, us for FC1 / FC2 / FC2 dgrad / recompute / FC1 dgrad:
+//   rows   256 x 256               128 x 128 walk          Thin walk
+//     16   112/ 44/ 38/142/121      81/ 39/ 32/106/123      73/ 40/ 36/ 92/135
+//     32   113/ 45/ 39/146/118      84/ 41/ 33/109/120      74/ 47/ 36/ 92/128
+//     64   118/ 51/ 45/150/140      84/ 58/ 35/108/151      89/ 48/ 47/101/138
+//    128   122/ 70/ 49/152/171     115/ 64/ 57/132/146     113/ 67/ 56/124/155
+//    256   150/ 92/ 79/173/200     153/ 86/ 72/174/189     179/104/ 94/196/230
+//    512   231/130/114/265/261     246/137/129/281/281     293/173/159/319/372
+// and at 4 rows, h 7168, F 2048: 354/257/179/368/453, 316/207/165/323/394,
+// 315/184/172/318/390 (FC1 there reads 1.88 GB: 0.36 ms at the copy rate).
+// Few rows per expert leave the weight tiles as the traffic: they want many
+// small tiles over the CUs and bytes in flight (Thin: 32 KB of weights per
+// workgroup ahead); many rows want operand reuse (256 x 256, one per CU).
+constexpr int kThinRows = 48, kMidRows = 320;
+// The weight gradients take 256 x 256 tiles unless the grid is too small to
+// give most CUs one.
+//
+// fp32: 64-row tiles up to kF32SmallGrid 128 x 128 tiles (2.5 rounds of the
+// 512 that are resident): 36 m-tiles x 8 (FC1 dgrad at 4096 slots, h 1024, F
+// 1408) left half the CUs with twice the others' work, 336 -> 256 us, and
+// 36 x 22 (FC1) 274 -> 237 us; past it the larger tile's operand reuse wins
+// (16384 slots, F 2048: 1103 against 1162 us for FC1).
+constexpr int kF32SmallGrid = 1280;
+//
 // Every problem takes direct copies into LDS: the dgrads (an activation-row
 // operand and a K-strided weight operand) and the router's dX measured 2-8 %
 // faster with them than with register-staged copies, which remain a launch
@@ -2050,19 +2105,28 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
 template <template <typename, class> class PT>
 hipError_t launch_auto(const GemmArgs& g_in, hipStream_t s) {
   GemmArgs g = g_in;
-  if (g.raster < 0) g.raster = PT<float, Big8>::kRaster;
-  if (g.dtype != 0) return launch_cfg<PT, Small>(g, s);
+  typedef PT<float, Big8> Any;
+  if (g.raster < 0) g.raster = Any::kRaster;
+  if (g.dtype != 0) {
+    typedef std::conditional_t<PairedColumns<Any>::value, F32P, F32N> SmallF32;
+    if (PT<float, Small>::grid(g) < kF32SmallGrid) return launch_tiles<float, PT, SmallF32>(g, s);
+    return launch_tiles<float, PT, Small>(g, s);
+  }
   switch (g.tile_override) {  // memfine_launch_options.tile
-    case 1: return launch_cfg<PT, Small>(g, s);
-    case 2: return launch_cfg<PT, Big8>(g, s);
-    case 3: return launch_cfg<PT, Big8R>(g, s);
+    case 1: return launch_tiles<bf16_t, PT, Small>(g, s);
+    case 2: return launch_tiles<bf16_t, PT, Big8>(g, s);
+    case 3: return launch_tiles<bf16_t, PT, Big8R>(g, s);
     default: break;
   }
-  if (PT<float, Big8>::grid(g) >= 128) {
-    if (g.split_tail) return launch_split_cfg<PT, Big8, Quarter8>(g, s);
-    return launch_cfg<PT, Big8>(g, s);
+  if constexpr (Any::kEqualTiles) {  // row-grouped
+    if (g.n <= (int64_t)kThinRows * g.E) return launch_walk<bf16_t, PT, Thin>(g, s);
+    if (g.n < (int64_t)kMidRows * g.E) return launch_walk<bf16_t, PT, Small>(g, s);
   }
-  return launch_cfg<PT, Small>(g, s);
+  if (Any::grid(g) >= 128) {
+    if (g.split_tail) return launch_split_cfg<PT, Big8, Quarter8>(g, s);
+    return launch_tiles<bf16_t, PT, Big8>(g, s);
+  }
+  return launch_tiles<bf16_t, PT, Small>(g, s);
 }
 
 template <template <typename, class> class P1, template <typename, class> class P2>

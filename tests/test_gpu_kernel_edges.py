@@ -61,3 +61,44 @@ def test_wgrad_tile_edges(mf, h, F, E, dtype, accumulate):
     log(f"wgrad edges h={h} F={F} E={E} {dtype} accumulate={accumulate}")
     for opts in ({}, {"tile": mf.TILE_256}) if dtype == "bf16" else ({},):
         _check_bwd(mf, w, 300 + h + F, 2, accumulate, **opts)
+
+
+# Tile shape by rows per expert (48 and 320 of an average expert): both sides
+# of each line, ragged and skewed loads, one row in all; and E = 80, where the
+# tiles are located by walking the experts.  Every shape gives the same bits.
+@pytest.mark.parametrize("T,E,h,F", [(1, 4, 192, 128), (96, 4, 320, 192), (97, 4, 320, 192),
+                                     (639, 4, 192, 320), (640, 4, 192, 320), (37, 80, 128, 64),
+                                     (2000, 80, 64, 128)])
+def test_tile_shape_by_rows(mf, T, E, h, F):
+    w = mw.Workload("rows", T=T, h=h, F=F, E=E, k=2, dtype="bf16", routing="dirichlet")
+    log(f"tile shape T={T} E={E} h={h} F={F}")
+    case = mw.make_case(w, 900 + T)
+    dev = device_case(w, case)
+    Y = host(run_fwd(w, dev, 1))
+    assert relerr(Y, om.moe_fwd(case["X"], case["idx"], case["gates"], case["W1"], case["W2"],
+                                1)) <= TOL["bf16"]
+    _check_bwd(mf, w, 900 + T, 1, False)
+    B = {k: host(v) for k, v in run_bwd(w, dev, 1).items()}
+    for tile in (mf.TILE_128, mf.TILE_256):
+        try:
+            mf.memfine_set_launch_options(tile=tile)
+            assert np.array_equal(host(run_fwd(w, dev, 1)), Y), tile
+            other = {k: host(v) for k, v in run_bwd(w, dev, 1).items()}
+        finally:
+            mf.memfine_set_launch_options()
+        for key in B:
+            assert np.array_equal(other[key], B[key]), (tile, key)
+
+
+# fp32: 64-row tiles below 1280 tiles of 128 x 128, the larger ones from there
+# (FC1: F / 64 = 256 column tiles x 4 and x 5 row tiles).
+@pytest.mark.parametrize("T", [512, 640])
+def test_f32_tile_shape_by_grid(mf, T):
+    w = mw.Workload("grid", T=T, h=64, F=16384, E=1, k=1, dtype="f32", routing="dirichlet")
+    log(f"f32 tile shape T={T}")
+    case = mw.make_case(w, 40 + T)
+    dev = device_case(w, case)
+    Y = host(run_fwd(w, dev, 1))
+    assert relerr(Y, om.moe_fwd(case["X"], case["idx"], case["gates"], case["W1"], case["W2"],
+                                1)) <= TOL["f32"]
+    _check_bwd(mf, w, 40 + T, 1, False)
