@@ -1183,16 +1183,12 @@ int memfine_router_fwd(const memfine_shape* shape, const void* d_X, const void* 
                                         d_logits, s));
   // Wide routers: the logits as a grouped GEMM on 256-token tiles (each tile
   // reads Wr once; one fused kernel per 32 tokens read it T / 32 times), then
-  // their top-k.  Working memory: the {0, T} row offsets of the GEMM's one
-  // "expert" and, without d_logits, the logits themselves.
-  const int64_t off_bytes = 256, lg_bytes = d_logits ? 0 : S.T * (int64_t)S.E * 4;
-  void* ws = ws_alloc(nullptr, (size_t)(off_bytes + lg_bytes), s);
-  if (!ws) return MEMFINE_ERR_OOM;
-  int32_t* off = (int32_t*)ws;
-  float* lg = d_logits ? d_logits : (float*)((char*)ws + off_bytes);
-  hipError_t err = launch_fill_i32(off, 1, 0, s);
-  if (err == hipSuccess) err = launch_fill_i32(off + 1, 1, (int32_t)S.T, s);
-  if (err == hipSuccess) {
+  // their top-k.  Working memory: without d_logits, the logits themselves.
+  const size_t lg_bytes = d_logits ? 0 : (size_t)(S.T * (int64_t)S.E * 4);
+  float* lg = d_logits ? d_logits : (float*)ws_alloc(nullptr, lg_bytes, s);
+  if (!lg) return MEMFINE_ERR_OOM;
+  hipError_t err;
+  {
     const memfine_launch_options opt = launch_options();
     GemmArgs g = {};
     g.dtype = S.dtype;
@@ -1200,7 +1196,6 @@ int memfine_router_fwd(const memfine_shape* shape, const void* d_X, const void* 
     g.E = 1;
     g.h = S.E;   // output columns: the logits
     g.F = S.h;   // reduction: the hidden size
-    g.offsets = off;
     g.a = const_cast<void*>(d_X);
     g.W2 = d_Wr;
     g.y = lg;
@@ -1212,7 +1207,7 @@ int memfine_router_fwd(const memfine_shape* shape, const void* d_X, const void* 
     err = launch_router_logits(g, s);
   }
   if (err == hipSuccess) err = launch_router_topk(lg, S.T, S.E, S.k, d_idx, d_gates, s);
-  ws_release(nullptr, ws, (size_t)(off_bytes + lg_bytes), s);
+  if (!d_logits) ws_release(nullptr, lg, lg_bytes, s);
   return hip_status(err);
 }
 
@@ -1234,9 +1229,11 @@ int memfine_router_bwd(const memfine_shape* shape, const void* d_X, const void* 
   if (!d_X || !d_idx || !d_gates || !d_dgates || !d_dX) return MEMFINE_ERR_INVALID_ARG;
   const int64_t es = elem_bytes(S), T = S.T;
   const int EP = router_ep(S.E);
-  // split-K: enough row ranges for about 256 workgroups, each at least 256 rows
+  // split-K: as many row ranges as give at most 256 workgroups (one round of
+  // the CUs: at 32768 tokens, h 7168, 10 ranges = 280 tiles took 215 us, 9 =
+  // 252 tiles 145 us), each at least 256 rows
   const int ntn = (S.h + 255) / 256;
-  const int64_t want = (256 + ntn - 1) / ntn, most = std::max<int64_t>(1, T / 256);
+  const int64_t want = std::max(1, 256 / ntn), most = std::max<int64_t>(1, T / 256);
   const int splits = (int)std::max<int64_t>(1, std::min(want, most));
   // dX (+)= dz Wr: per token in the dz kernel, or (E % 64 == 0, so that the
   // dense dz rows are whole K tiles) as a grouped GEMM from D, which reads
@@ -1245,8 +1242,7 @@ int memfine_router_bwd(const memfine_shape* shape, const void* d_X, const void* 
   const int64_t o_meta = align256(T * EP * es);
   const int64_t o_order = o_meta + align256((splits + 1) * 4);
   const int64_t o_tok = o_order + align256(splits * 4);
-  const int64_t o_off1 = o_tok + align256(T * 4);
-  const int64_t o_part = o_off1 + 256;
+  const int64_t o_part = o_tok + align256(T * 4);
   const int64_t total = o_part + align256((int64_t)splits * EP * S.h * 4);
   char* ws = (char*)ws_alloc(alloc, (size_t)total, s);
   if (!ws) return MEMFINE_ERR_OOM;
@@ -1254,41 +1250,36 @@ int memfine_router_bwd(const memfine_shape* shape, const void* d_X, const void* 
   int32_t* offsets = (int32_t*)(ws + o_meta);
   int32_t* order = (int32_t*)(ws + o_order);
   int32_t* tok = (int32_t*)(ws + o_tok);
-  int32_t* off1 = (int32_t*)(ws + o_off1);
   float* part = (float*)(ws + o_part);
   const double Td = (double)T, hd = (double)S.h;
-  hipError_t err = launch_router_split_meta(offsets, order, tok, T, splits, s);
-  if (err == hipSuccess) {
+  hipError_t err;
+  {
     KernelTimer kt(MEMFINE_K_ROUTER_BWD_DX, s, 2.0 * Td * (gemm_dx ? EP : S.k) * hd,
                    (double)es * (Td * hd * (accumulate_dX ? 2.0 : 1.0) +
                                  Td * EP * (gemm_dx ? 2.0 : 1.0) + (double)S.E * hd) +
                        12.0 * Td * S.k);
-    err = launch_router_bwd_dx(S.dtype, d_Wr, d_idx, d_gates, d_dgates, T, S.h, S.E, S.k,
-                               EP, accumulate_dX, gemm_dx ? 0 : 1, d_dX, D, s);
+    const RouterSplit sp = {offsets, order, tok, splits};
+    err = gemm_dx ? launch_router_dz(S.dtype, d_idx, d_gates, d_dgates, T, S.E, S.k, EP, D, sp, s)
+                  : launch_router_bwd_dx(S.dtype, d_Wr, d_idx, d_gates, d_dgates, T, S.h, S.E, S.k,
+                                         EP, accumulate_dX, d_dX, D, sp, s);
     if (err == hipSuccess && gemm_dx) {
-      err = launch_fill_i32(off1, 1, 0, s);
-      if (err == hipSuccess) err = launch_fill_i32(off1 + 1, 1, (int32_t)T, s);
-      if (err == hipSuccess) {
-        const memfine_launch_options opt = launch_options();
-        GemmArgs g = {};
-        g.dtype = S.dtype;
-        g.n = (int)T;
-        g.E = 1;
-        g.h = EP;    // reduction: the dense dz row
-        g.F = S.h;   // output columns: the hidden size
-        g.offsets = off1;
-        g.tok_of_row = tok;   // the identity
-        g.dY = D;
-        g.W2 = d_Wr;
-        g.ag = d_dX;
-        g.accumulate = accumulate_dX;
-        g.T_h_bytes = T * (int64_t)EP * es;
-        g.tile_override = opt.tile;
-        g.raster = opt.raster;
-        g.cus = device_cus();
-        g.split_tail = opt.split_tail;
-        err = launch_router_dx(g, s);
-      }
+      const memfine_launch_options opt = launch_options();
+      GemmArgs g = {};
+      g.dtype = S.dtype;
+      g.n = (int)T;
+      g.E = 1;
+      g.h = EP;    // reduction: the dense dz row
+      g.F = S.h;   // output columns: the hidden size
+      g.dY = D;
+      g.W2 = d_Wr;
+      g.ag = d_dX;
+      g.accumulate = accumulate_dX;
+      g.T_h_bytes = T * (int64_t)EP * es;
+      g.tile_override = opt.tile;
+      g.raster = opt.raster;
+      g.cus = device_cus();
+      g.split_tail = opt.split_tail;
+      err = launch_router_dx(g, s);
     }
   }
   if (err == hipSuccess) {

@@ -52,6 +52,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "memfine.h"
 
 namespace memfine {
 namespace {
@@ -597,11 +598,13 @@ inline int row_tiles_bound(int n, int E, int BM) {
 // over the experts.  All lanes of the wave must call these together.
 template <int BM> struct RowTiles {
   int o0 = 0, o1 = 0, n = 0, inc = 0, total = 0;
-  __device__ __forceinline__ void load(const int32_t* __restrict__ offsets, int E) {
+  __device__ __forceinline__ void load(const GemmArgs& g) {
     const int lane = threadIdx.x & 63;
-    if (lane < E) {
-      o0 = offsets[lane];
-      o1 = offsets[lane + 1];
+    if (g.offsets == nullptr) {  // one group of all n rows
+      if (lane == 0) o1 = g.n;
+    } else if (lane < g.E) {
+      o0 = g.offsets[lane];
+      o1 = g.offsets[lane + 1];
     }
     n = (o1 - o0 + BM - 1) / BM;
     inc = n;
@@ -628,26 +631,22 @@ template <int BM> struct RowTiles {
 };
 
 // m-tiles of a row-grouped grid: sum_e ceil(c_e / BM).
-template <int BM> __device__ __forceinline__ int row_tiles(const int32_t* __restrict__ offsets, int E) {
-  if (E <= 64) {
+template <int BM> __device__ __forceinline__ int row_tiles(const GemmArgs& g) {
+  if (g.E <= 64) {
     RowTiles<BM> rt;
-    rt.load(offsets, E);
+    rt.load(g);
     return rt.total;
   }
   int n = 0;
-  for (int e = 0; e < E; ++e) n += (offsets[e + 1] - offsets[e] + BM - 1) / BM;
+  for (int e = 0; e < g.E; ++e) n += (g.offsets[e + 1] - g.offsets[e] + BM - 1) / BM;
   return n;
 }
 
-// Expert and rows of m-tile `mt` of a row-grouped problem.
+// Expert and rows of m-tile `mt` of a row-grouped problem with more experts
+// than a wave has lanes.
 template <int BM>
 __device__ __forceinline__ bool locate_rows(const int32_t* __restrict__ offsets, int E, int mt,
                                             Tile& t) {
-  if (E <= 64) {
-    RowTiles<BM> rt;
-    rt.load(offsets, E);
-    return rt.locate(mt, t);
-  }
   int acc = 0;
   for (int e = 0; e < E; ++e) {
     const int r0 = offsets[e], r1 = offsets[e + 1];
@@ -673,12 +672,12 @@ __device__ __forceinline__ bool locate_grid(const GemmArgs& g, int L, int ntn, T
   int mt;
   if (g.E <= 64) {
     RowTiles<BM> rt;
-    rt.load(g.offsets, g.E);
+    rt.load(g);
     if (L >= rt.total * ntn) return false;
     logical_coords(g.raster, L, rt.total, ntn, mt, nt);
     return rt.locate(mt, t);
   }
-  const int mtn = row_tiles<BM>(g.offsets, g.E);
+  const int mtn = row_tiles<BM>(g);
   if (L >= mtn * ntn) return false;
   logical_coords(g.raster, L, mtn, ntn, mt, nt);
   return locate_rows<BM>(g.offsets, g.E, mt, t);
@@ -832,7 +831,7 @@ template <typename T, class C, bool kBwd> struct ProbFC1 {
     return locate_row_subtile<ProbSelf, C::BM, BNU>(g, t, b, sub);
   }
   __device__ __forceinline__ static int total_tiles(const GemmArgs& g) {
-    return row_tiles<C::BM>(g.offsets, g.E) * ((ncols(g) + BNU - 1) / BNU);
+    return row_tiles<C::BM>(g) * ((ncols(g) + BNU - 1) / BNU);
   }
   __device__ __forceinline__ bool active(const GemmArgs& g, const Tile& t, int wm, int wn) const {
     return row_wave_active<ProbSelf, C, BNU>(g, t, wm, wn);
@@ -1013,7 +1012,7 @@ template <typename T, class C> struct ProbFC2 {
     return locate_row_subtile<ProbSelf, C::BM, BNU>(g, t, b, sub);
   }
   __device__ __forceinline__ static int total_tiles(const GemmArgs& g) {
-    return row_tiles<C::BM>(g.offsets, g.E) * ((ncols(g) + BNU - 1) / BNU);
+    return row_tiles<C::BM>(g) * ((ncols(g) + BNU - 1) / BNU);
   }
   __device__ __forceinline__ bool active(const GemmArgs& g, const Tile& t, int wm, int wn) const {
     return row_wave_active<ProbSelf, C, BNU>(g, t, wm, wn);
@@ -1046,7 +1045,7 @@ template <typename T, class C> struct ProbFC2 {
 };
 
 // Router logits: logits[t, e] = sum_k X[t, k] Wr[e, k], stored in fp32.
-// FC2's problem with one "expert" holding all T rows: X in `a` (K = h in
+// FC2's problem with one group of all T rows (no offsets): X in `a` (K = h in
 // GemmArgs.F), Wr in `W2` (its E_r rows in GemmArgs.h), the logits in `y`.
 template <typename T, class C> struct ProbLogits : ProbFC2<T, C> {
   __device__ __forceinline__ void epilogue(const GemmArgs& g, const Tile& t, const Accum<C>& acc,
@@ -1079,7 +1078,7 @@ template <typename T, class C> struct ProbFC2Dgrad {
     return locate_row_subtile<ProbSelf, C::BM, BNU>(g, t, b, sub);
   }
   __device__ __forceinline__ static int total_tiles(const GemmArgs& g) {
-    return row_tiles<C::BM>(g.offsets, g.E) * ((ncols(g) + BNU - 1) / BNU);
+    return row_tiles<C::BM>(g) * ((ncols(g) + BNU - 1) / BNU);
   }
   __device__ __forceinline__ bool active(const GemmArgs& g, const Tile& t, int wm, int wn) const {
     return row_wave_active<ProbSelf, C, BNU>(g, t, wm, wn);
@@ -1087,9 +1086,12 @@ template <typename T, class C> struct ProbFC2Dgrad {
   __host__ __device__ static int reduction(const GemmArgs& g) { return g.h; }
   __device__ __forceinline__ void init(const GemmArgs& g, const Tile& t, int wave, int lane) {
     A.rs = make_rsrc(g.dY, g.T_h_bytes);
-    const int32_t* tok = g.tok_of_row + t.m0;
+    const int32_t* tok = g.tok_of_row;
     const uint32_t rowb = (uint32_t)g.h * sizeof(T);
-    A.init([&](int r) { return r < t.mrows ? (uint32_t)tok[r] * rowb : kOOB; }, wave, lane);
+    if (tok == nullptr)  // row m is token m
+      A.init([&](int r) { return r < t.mrows ? (uint32_t)(t.m0 + r) * rowb : kOOB; }, wave, lane);
+    else
+      A.init([&](int r) { return r < t.mrows ? (uint32_t)tok[t.m0 + r] * rowb : kOOB; }, wave, lane);
     const uint32_t ld = (uint32_t)g.F * sizeof(T);  // W2[e] row o holds F values
     B.rs = make_rsrc(cptr<T>(g.W2, (int64_t)t.e * g.h * g.F), (int64_t)g.h * ld);
 #pragma clang loop unroll(full)
@@ -1120,8 +1122,7 @@ template <typename T, class C> struct ProbFC2Dgrad {
 
 // Router backward's input gradient: dX[t, n] (+)= sum_e D[t, e] Wr[e, n],
 // with D the dense dz rows [T, E] (E % 64 == 0).  FC2 dgrad's problem with
-// one "expert" of T rows: D in `dY` (K = E in GemmArgs.h, rows through the
-// identity `tok_of_row`), Wr in `W2` (h columns in GemmArgs.F), dX in `ag`,
+// one group of T rows: D in `dY` (K = E in GemmArgs.h, no `tok_of_row`), Wr in `W2` (h columns in GemmArgs.F), dX in `ag`,
 // overwritten or, with `accumulate`, added to in fp32.
 template <typename T, class C> struct ProbRouterDx : ProbFC2Dgrad<T, C> {
   // reads dX when accumulating; the epilogue then has kStageSlabBytes of the
@@ -1229,7 +1230,7 @@ template <typename T, class C> struct ProbFC1Dgrad {
     return locate_row_subtile<ProbSelf, C::BM, BNU>(g, t, b, sub);
   }
   __device__ __forceinline__ static int total_tiles(const GemmArgs& g) {
-    return row_tiles<C::BM>(g.offsets, g.E) * ((ncols(g) + BNU - 1) / BNU);
+    return row_tiles<C::BM>(g) * ((ncols(g) + BNU - 1) / BNU);
   }
   __device__ __forceinline__ bool active(const GemmArgs& g, const Tile& t, int wm, int wn) const {
     return row_wave_active<ProbSelf, C, BNU>(g, t, wm, wn);
@@ -2040,6 +2041,7 @@ inline double rounds(int tiles, int per_cu) {
 
 using Big8 = Cfg<256, 256, 2, 4, 2>;        // 8 waves of 128 x 64
 using Big8R = Cfg<256, 256, 2, 4, 2, 128, 0>;  // Big8 with register-staged copies
+using Mid8 = Cfg<128, 256, 2, 4, 3>;         // 8 waves of 64 x 64, three stages
 using Thin = Cfg<64, 128, 2, 2, 3>;         // 4 waves of 32 x 64, three stages, two per CU
 using F32N = Cfg<64, 64, 2, 2, 2>;          // fp32: 4 waves of 32 x 32, five per CU
 using F32P = Cfg<64, 128, 2, 2, 2>;         // fp32 FC1 (gate and up columns): 32 x 64, three per CU
@@ -2063,8 +2065,12 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
     const hipError_t err = launch_fill_i32(g.tile_ctr, 1, 0, s);
     if (err != hipSuccess) return err;
   }
-  const int blocks = (kPersistent<C, PT<bf16_t, C>> || dynamic) ? std::min(bound, g.cus)
-                                                                 : bound + 3 * (g.cus / 2);
+  // (a grid of at most cus / 2 tiles runs as 4 bound quarter tiles: with one
+  // workgroup per tile half of the CUs or more had none - 128 tiles of the
+  // router's logits at 32768 tokens, h 7168: 409 us, one round of 256: 255 us)
+  const int blocks = (kPersistent<C, PT<bf16_t, C>> || dynamic)
+                         ? (int)std::min<int64_t>(4ll * bound, g.cus)
+                         : bound + 3 * (g.cus / 2);
   grouped_gemm_split_kernel<bf16_t, C, CQ, PT<bf16_t, C>, PT<bf16_t, CQ>>
       <<<blocks, C::kThreads, 0, s>>>(g);
   return hipGetLastError();
@@ -2160,6 +2166,17 @@ hipError_t launch_router_dx(const GemmArgs& g, hipStream_t s) {
   return launch_auto<ProbRouterDx>(g, s);
 }
 hipError_t launch_router_logits(const GemmArgs& g, hipStream_t s) {
+  // At most 256 columns, so the rows have to fill the chip: the smallest of
+  // the three tile heights that takes one round.  Measured at 256 logits, h
+  // 7168, us for 256 x 256 / 128 x 256 / 64 x 128 tiles: 8192 tokens 106 / 112
+  // / 61, 16384 112 / 117 / 104, 32768 409 / 140 / 204 (the first as quarter
+  // tiles), 65536 255 / 289 / 398, 131072 483 / 530 / 764.
+  if (g.dtype == 0 && g.tile_override == MEMFINE_TILE_AUTO) {
+    GemmArgs a = g;
+    if (a.raster < 0) a.raster = ProbLogits<float, Big8>::kRaster;
+    if (ProbLogits<bf16_t, Thin>::grid(a) <= 2 * a.cus) return launch_walk<bf16_t, ProbLogits, Thin>(a, s);
+    if (ProbLogits<bf16_t, Mid8>::grid(a) <= a.cus) return launch_walk<bf16_t, ProbLogits, Mid8>(a, s);
+  }
   return launch_auto<ProbLogits>(g, s);
 }
 hipError_t launch_fc1_dgrad_wgrad(const GemmArgs& g, hipStream_t s) {

@@ -78,9 +78,9 @@ hipError_t launch_unpermute_rows(int dtype, const void* dxp, const float* dgp, i
 struct GemmArgs {
   int dtype;
   int n, E, h, F;
-  const int32_t* offsets;
+  const int32_t* offsets;     // null: one group of all n rows (E = 1; not the weight gradients)
   const int32_t* order;
-  const int32_t* tok_of_row;
+  const int32_t* tok_of_row;  // null (FC2 dgrad only): row m is token m
   const float* gate_of_row;
   const void* X;     // [T, h]
   const void* dY;    // [T, h]
@@ -114,25 +114,32 @@ int dgate_partials(int F);
 hipError_t launch_router_fwd(int dtype, const void* X, const void* Wr, int64_t T, int h, int E,
                              int k, int32_t* idx, float* gates, float* logits, hipStream_t s);
 // Router forward in two steps for wide routers: the logits [T, E] (fp32) as a
-// grouped GEMM (launch_router_logits: one "expert" of T rows; X in a, K = h
-// in F, Wr in W2, E in h, logits in y, offsets {0, T}), then their top-k
+// grouped GEMM (launch_router_logits: one group of T rows, no offsets; X in a,
+// K = h in F, Wr in W2, E in h, logits in y), then their top-k
 // (64 < E <= 256, k <= 16) with the selection and gates of launch_router_fwd.
 hipError_t launch_router_logits(const GemmArgs& g, hipStream_t s);
 hipError_t launch_router_topk(const float* logits, int64_t T, int E, int k, int32_t* idx,
                               float* gates, hipStream_t s);
-// Router backward, per token: the dense dz rows D [T, EP] and, with
-// `with_dx`, dX (+)= dz Wr (else launch_router_dx computes it from D).
+// The split-K weight gradient's tables, written beside the dz rows: the row
+// ranges of S splits of the T rows (offsets [S + 1], order [S]) and the
+// identity row -> token table [T].
+struct RouterSplit {
+  int32_t *offsets, *order, *tok;
+  int S;
+};
+// Router backward, per token: the dense dz rows D [T, EP] (launch_router_dz),
+// and dX (+)= dz Wr with them (launch_router_bwd_dx).
+hipError_t launch_router_dz(int dtype, const int32_t* idx, const float* gates, const float* dgates,
+                            int64_t T, int E, int k, int EP, void* D, const RouterSplit& sp,
+                            hipStream_t s);
 hipError_t launch_router_bwd_dx(int dtype, const void* Wr, const int32_t* idx, const float* gates,
                                 const float* dgates, int64_t T, int h, int E, int k, int EP,
-                                int accumulate, int with_dx, void* dX, void* D, hipStream_t s);
-// dX (+)= D Wr as a grouped GEMM (E % 64 == 0): one "expert" of T rows; D in
-// dY (K = E in h, identity tok_of_row), Wr in W2, the hidden size in F, dX in
+                                int accumulate, void* dX, void* D, const RouterSplit& sp,
+                                hipStream_t s);
+// dX (+)= D Wr as a grouped GEMM (E % 64 == 0): one group of T rows; D in
+// dY (K = E in h, no tok_of_row), Wr in W2, the hidden size in F, dX in
 // ag, `accumulate` adds to it.
 hipError_t launch_router_dx(const GemmArgs& g, hipStream_t s);
-// Row ranges of S splits of T rows (offsets [S + 1], order [S]) and the
-// identity row -> token table [T], for the split-K weight gradient.
-hipError_t launch_router_split_meta(int32_t* offsets, int32_t* order, int32_t* tok, int64_t T, int S,
-                                    hipStream_t s);
 // dWr (+)= sum over the S partial products P [S, EP, h].
 hipError_t launch_router_reduce(const float* P, int S, int EP, int E, int h, int accumulate,
                                 float* dWr, hipStream_t s);

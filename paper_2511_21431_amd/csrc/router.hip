@@ -77,32 +77,30 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_fwd_kernel(
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[nb][q] = 0.f;
-  typename K::Raw a[2], b[2][NB];
+  // this wave's K blocks: w, w + W, w + 2W, ...; the operands of the next
+  // D - 1 blocks are in flight (at 4096 tokens, h 2048, 64 logits a wave has 8
+  // blocks to go through: three ahead 29 us, one ahead 33; with 32 logits or
+  // fewer one ahead is as fast)
+  constexpr int W = kRouterWaves, D = NB == 2 ? 4 : 2;
+  typename K::Raw a[D], b[D][NB];
   const int nkb = h / K::KB;
-  constexpr int W = kRouterWaves;
-  // this wave's K blocks: w, w + W, w + 2W, ...
-  if (w < nkb) {
-    K::load(xr, w, hh, a[0]);
+  auto fetch = [&](int d, int kb) {
+    if (kb < nkb) {
+      K::load(xr, kb, hh, a[d]);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) K::load(wr[nb], w, hh, b[0][nb]);
-  }
-  for (int kb = w; kb < nkb; kb += 2 * W) {
-    if (kb + W < nkb) {
-      K::load(xr, kb + W, hh, a[1]);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) K::load(wr[nb], kb + W, hh, b[1][nb]);
+      for (int nb = 0; nb < NB; ++nb) K::load(wr[nb], kb, hh, b[d][nb]);
     }
+  };
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) K::mma(a[0], b[0][nb], acc[nb]);
-    if (kb + W >= nkb) break;
-    if (kb + 2 * W < nkb) {
-      K::load(xr, kb + 2 * W, hh, a[0]);
+  for (int d = 0; d + 1 < D; ++d) fetch(d, w + d * W);
+  for (int kb = w; kb < nkb; kb += D * W)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) K::load(wr[nb], kb + 2 * W, hh, b[0][nb]);
+    for (int d = 0; d < D; ++d) {
+      if (kb + d * W >= nkb) break;
+      fetch((d + D - 1) % D, kb + (d + D - 1) * W);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) K::mma(a[d], b[d][nb], acc[nb]);
     }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) K::mma(a[1], b[1][nb], acc[nb]);
-  }
   // partial products of waves 1..W-1 to LDS, summed by wave 0 in wave order
   if (w > 0) {
 #pragma unroll
@@ -184,88 +182,84 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_fwd_kernel(
 __device__ __forceinline__ float lane_value(float v, int j) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j));
 }
-// One step of a (value, lower index) arg-max with the lane that DPP control
-// `kCtrl` names (a permutation inside each row of 16 lanes).
-template <int kCtrl>
-__device__ __forceinline__ void argmax_dpp(float& v, int& i) {
-  const float ov = __builtin_bit_cast(
-      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
-  const int oi = __builtin_amdgcn_update_dpp(0, i, kCtrl, 0xf, 0xf, false);
-  if (ov > v || (ov == v && oi < i)) {
-    v = ov;
-    i = oi;
-  }
+// Order-preserving key of a logit (larger logit, larger key; -0 as +0); 0, below
+// every logit's key, for a NaN, which is never selected.
+__device__ __forceinline__ uint32_t logit_key(float v) {
+  const uint32_t u = __float_as_uint(v + 0.f);
+  return v != v ? 0u : (u >> 31) ? ~u : u | 0x80000000u;
 }
-// The wave's arg-max over (value, lower index), left in every lane: inside
-// each row of 16 lanes by DPP (swap neighbours, swap pairs, mirror halves of
-// 8, mirror the row: after each step a lane holds the best of 2, 4, 8, 16
-// lanes), then the four rows' results through scalar registers.
-__device__ __forceinline__ void wave_argmax(float& v, int& i) {
-  argmax_dpp<0xb1>(v, i);   // quad_perm [1, 0, 3, 2]
-  argmax_dpp<0x4e>(v, i);   // quad_perm [2, 3, 0, 1]
-  argmax_dpp<0x141>(v, i);  // row_half_mirror
-  argmax_dpp<0x140>(v, i);  // row_mirror
-  float bv = lane_value(v, 0);
-  int bi = __builtin_amdgcn_readlane(i, 0);
+__device__ __forceinline__ float key_logit(uint32_t key) {
+  return __uint_as_float((key >> 31) ? key ^ 0x80000000u : ~key);
+}
+template <int kCtrl> __device__ __forceinline__ uint32_t max_dpp(uint32_t v) {
+  const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, false);
+  return o > v ? o : v;
+}
+// The wave's largest key, in a scalar register: inside each row of 16 lanes by
+// DPP (swap neighbours, swap pairs, mirror halves of 8, mirror the row), then
+// the four rows' results.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max_dpp<0xb1>(v);   // quad_perm [1, 0, 3, 2]
+  v = max_dpp<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+  v = max_dpp<0x141>(v);  // row_half_mirror
+  v = max_dpp<0x140>(v);  // row_mirror
+  uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
 #pragma unroll
-  for (int r = 16; r < 64; r += 16) {
-    const float ov = lane_value(v, r);
-    const int oi = __builtin_amdgcn_readlane(i, r);
-    if (ov > bv || (ov == bv && oi < bi)) {
-      bv = ov;
-      bi = oi;
-    }
-  }
-  v = bv;
-  i = bi;
+  for (int r = 16; r < 64; r += 16) m = max(m, (uint32_t)__builtin_amdgcn_readlane((int)v, r));
+  return m;
 }
 
 // Top-k of one token whose logits a wave holds (lane l: experts l + 64 q,
-// q < V; entries of experts >= E are ignored): k rounds of a wave-wide
-// arg-max over (logit, lower id), so the selection and its order are those
-// of the narrow kernel; then lanes 0..k-1 write the
-// selected ids, largest first, and the gates renormalised over them (the
-// full softmax's denominator cancels).
+// q < V; entries of experts >= E are ignored): k rounds of the wave's largest
+// key, then the lowest expert id that holds it (ids rise with q, then with the
+// lane), so the selection and its order are those of the narrow kernel.  Lane
+// j keeps round j's id and logit and writes them with the gates renormalised
+// over the selected (the full softmax's denominator cancels).  Bound by the
+// vector instructions of the rounds: an arg-max carrying (value, id) pairs
+// through every step took about twice as many (131072 tokens, 256 logits, 8
+// rounds: 201 us, now 89; 134 MB of logits read).
 template <int V>
 __device__ __forceinline__ void wave_topk(const float (&v)[V], int E, int k, int lane, int64_t t,
                                           int32_t* __restrict__ idx, float* __restrict__ gates) {
-  uint32_t taken = 0;
-  float selv[16];
-  int seli[16];
+  uint32_t key[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) key[q] = lane + 64 * q < E ? logit_key(v[q]) : 0u;
+  float myv = 0.f, top = 0.f;
+  int myi = 0;
   for (int j = 0; j < k; ++j) {
-    float bv = -INFINITY;
-    int bi = INT32_MAX;
+    uint32_t m = key[0];
 #pragma unroll
-    for (int q = 0; q < V; ++q) {
-      const int e = lane + 64 * q;
-      if (e < E && !((taken >> q) & 1u) && (v[q] > bv || (v[q] == bv && e < bi))) {
-        bv = v[q];
-        bi = e;
+    for (int q = 1; q < V; ++q) m = max(m, key[q]);
+    m = wave_max(m);
+    int q = V, l = 0;  // the winner: expert l + 64 q
+#pragma unroll
+    for (int qq = V - 1; qq >= 0; --qq) {
+      const uint64_t b = __ballot(key[qq] == m);
+      if (b != 0) {
+        q = qq;
+        l = __builtin_ctzll(b);
       }
     }
-    wave_argmax(bv, bi);
-    if ((bi & 63) == lane) taken |= 1u << (bi >> 6);
+    // fewer than k numbers among the logits: no expert
+    const float bv = m != 0 ? key_logit(m) : -INFINITY;
+    const int bi = m != 0 ? l + 64 * q : INT32_MAX;
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj)
-      if (jj == j) {
-        selv[jj] = bv;
-        seli[jj] = bi;
-      }
+    for (int qq = 0; qq < V; ++qq)
+      if (lane == l && qq == q) key[qq] = 0;
+    if (j == 0) top = bv;
+    if (lane == j) {
+      myv = bv;
+      myi = bi;
+    }
   }
-  // renormalised softmax over the selected logits; selv[0] is the largest
-  float e[16], sum = 0.f;
-#pragma unroll
-  for (int jj = 0; jj < 16; ++jj) {
-    e[jj] = jj < k ? __expf(selv[jj] - selv[0]) : 0.f;
-    sum += e[jj];
-  }
+  const float e = lane < k ? __expf(myv - top) : 0.f;
+  float sum = 0.f;
+  for (int j = 0; j < k; ++j) sum += lane_value(e, j);
   const float inv = 1.f / sum;
-#pragma unroll
-  for (int jj = 0; jj < 16; ++jj)
-    if (jj < k && lane == jj) {
-      idx[t * k + jj] = seli[jj];
-      gates[t * k + jj] = e[jj] * inv;
-    }
+  if (lane < k) {
+    idx[t * k + lane] = myi;
+    gates[t * k + lane] = e * inv;
+  }
 }
 
 // Forward for wide routers (64 < E <= 256 logits per token, the width of a
@@ -366,7 +360,79 @@ __global__ __launch_bounds__(256) void router_topk_kernel(const float* __restric
   wave_topk<V>(v, E, k, lane, t, idx, gates);
 }
 
-// Backward, one wave per token (grid-stride): dz_j = g_j (dg_j - sum g dg);
+// The first workgroup writes the row ranges of the split-K weight gradient.
+__device__ __forceinline__ void write_split(const RouterSplit& sp, int64_t T_) {
+  if (blockIdx.x != 0) return;
+  for (int s = threadIdx.x; s <= sp.S; s += blockDim.x) {
+    sp.offsets[s] = (int32_t)(s * T_ / sp.S);
+    if (s < sp.S) sp.order[s] = s;
+  }
+}
+
+// Dense dz rows alone (dX then is a GEMM from them): a workgroup writes kDzTokens
+// rows of D.  Thread t < kDzTokens computes its token's dz_j = g_j (dg_j - sum g
+// dg) and puts them into a zeroed LDS image of the rows, which all threads
+// then copy out in 16-byte units: bound by the write of D (one wave per token
+// building its row by comparing every column with every slot: 48 us at
+// 32768 tokens, 256 logits, now 10 for 17 MB).
+constexpr int kDzTokens = 64;
+template <typename T>
+__global__ __launch_bounds__(256) void router_dz_kernel(
+    const int32_t* __restrict__ idx, const float* __restrict__ gates,
+    const float* __restrict__ dgates, int64_t T_, int E, int k, int EP, T* __restrict__ D,
+    RouterSplit sp) {
+  extern __shared__ u32x4_t rows16[];  // kDzTokens rows of EP elements
+  T* rows = (T*)rows16;
+  const int64_t t0 = (int64_t)blockIdx.x * kDzTokens;
+  const int nt = (int)min((int64_t)kDzTokens, T_ - t0);
+  const int units = kDzTokens * EP * (int)sizeof(T) / 16;
+  write_split(sp, T_);
+  float dz[16];
+  int id[16];
+  const bool mine = (int)threadIdx.x < nt;
+  const int64_t t = t0 + threadIdx.x;
+  if (mine) {
+    sp.tok[t] = (int32_t)t;
+    float g[16], gd[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int i = j < k ? idx[t * k + j] : -1;
+      id[j] = i >= 0 && i < E ? i : -1;  // a slot whose id lies outside [0, E) is dropped
+      g[j] = id[j] >= 0 ? gates[t * k + j] : 0.f;
+      dz[j] = id[j] >= 0 ? dgates[t * k + j] : 0.f;
+      gd[j] = g[j] * dz[j];
+    }
+#pragma unroll
+    for (int w = 1; w < 16; w <<= 1)  // a pairwise tree
+#pragma unroll
+      for (int j = 0; j < 16; j += 2 * w) gd[j] += gd[j + w];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) dz[j] = g[j] * (dz[j] - gd[0]);
+  }
+  for (int u = threadIdx.x; u < units; u += 256) rows16[u] = (u32x4_t){0, 0, 0, 0};
+  __syncthreads();
+  if (mine) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      if (id[j] < 0) continue;
+      float v = dz[j];
+      bool first = true;  // slots of one token with the same id add up
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (i < j && id[i] == id[j]) first = false;
+        if (i > j && id[i] == id[j]) v += dz[i];
+      }
+      if (!first) continue;
+      if constexpr (sizeof(T) == 2) rows[threadIdx.x * EP + id[j]] = (T)(pack_bf16x2(v, 0.f) & 0xffffu);
+      else rows[threadIdx.x * EP + id[j]] = v;
+    }
+  }
+  __syncthreads();
+  u32x4_t* out = (u32x4_t*)(D + t0 * EP);
+  for (int u = threadIdx.x; u < nt * EP * (int)sizeof(T) / 16; u += 256) out[u] = rows16[u];
+}
+
+// Backward with its dX, one wave per token (grid-stride): dz_j = g_j (dg_j - sum g dg);
 // dX[t] (+)= sum_j dz_j Wr[i_j]; the dense row D[t, 0..EP) = dz scattered to
 // the selected experts (bf16 or fp32, zero elsewhere) for the weight-gradient
 // GEMM.  Lane j < k loads slot j and the k values are broadcast by shuffles;
@@ -376,16 +442,18 @@ template <typename T>
 __global__ __launch_bounds__(256) void router_bwd_dx_kernel(
     const T* __restrict__ Wr, const int32_t* __restrict__ idx, const float* __restrict__ gates,
     const float* __restrict__ dgates, int64_t T_, int h, int E, int k, int EP, int accumulate,
-    int with_dx, T* __restrict__ dX, T* __restrict__ D) {
+    T* __restrict__ dX, T* __restrict__ D, RouterSplit sp) {
   constexpr int V = Elem<T>::kVec;  // elements per 16-byte vector
   constexpr int NV = 4;             // vectors per lane per pass
   const int lane = threadIdx.x & 63;
   const int64_t waves = (int64_t)gridDim.x * 4;
+  write_split(sp, T_);
   for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < T_; t += waves) {
     // slot `lane` (lanes < k); a slot whose id lies outside [0, E) is dropped
     const int i = lane < k ? idx[t * k + lane] : -1;
     const bool in = i >= 0 && i < E;
     const float g = in ? gates[t * k + lane] : 0.f, d = in ? dgates[t * k + lane] : 0.f;
+    if (lane == 0) sp.tok[t] = (int32_t)t;
     // sum over the k <= 16 slots held by lanes 0..15, read into scalar
     // registers (v_readlane) and added as a pairwise tree
     float gd[16];
@@ -407,7 +475,7 @@ __global__ __launch_bounds__(256) void router_bwd_dx_kernel(
       dzs[j] = lane_value(dz, j);
       ids[j] = j < k ? __builtin_amdgcn_readlane(id, j) : -1;
     }
-    for (int c0 = lane * V; with_dx && c0 < h; c0 += 64 * V * NV) {
+    for (int c0 = lane * V; c0 < h; c0 += 64 * V * NV) {
       float acc[NV][V];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -485,16 +553,6 @@ __global__ __launch_bounds__(256) void router_reduce_kernel(const float* __restr
   *(f32x4_t*)(dWr + el) = acc;
 }
 
-__global__ void iota_kernel(int32_t* p, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = i;
-}
-__global__ void split_offsets_kernel(int32_t* offsets, int32_t* order, int64_t T_, int S) {
-  const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s <= S) offsets[s] = (int32_t)(s * T_ / S);
-  if (s < S) order[s] = s;
-}
-
 }  // namespace
 
 hipError_t launch_router_fwd(int dtype, const void* X, const void* Wr, int64_t T, int h, int E,
@@ -534,25 +592,34 @@ hipError_t launch_router_topk(const float* logits, int64_t T, int E, int k, int3
   return hipGetLastError();
 }
 
+hipError_t launch_router_dz(int dtype, const int32_t* idx, const float* gates, const float* dgates,
+                            int64_t T, int E, int k, int EP, void* D, const RouterSplit& sp,
+                            hipStream_t s) {
+  if (T == 0) return hipSuccess;
+  if (k > 16 || EP > 256) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)((T + kDzTokens - 1) / kDzTokens);
+  if (dtype == 0)
+    router_dz_kernel<bf16_t><<<blocks, 256, kDzTokens * EP * 2, s>>>(idx, gates, dgates, T, E, k, EP,
+                                                                     (bf16_t*)D, sp);
+  else
+    router_dz_kernel<float><<<blocks, 256, kDzTokens * EP * 4, s>>>(idx, gates, dgates, T, E, k, EP,
+                                                                    (float*)D, sp);
+  return hipGetLastError();
+}
+
 hipError_t launch_router_bwd_dx(int dtype, const void* Wr, const int32_t* idx, const float* gates,
                                 const float* dgates, int64_t T, int h, int E, int k, int EP,
-                                int accumulate, int with_dx, void* dX, void* D, hipStream_t s) {
+                                int accumulate, void* dX, void* D, const RouterSplit& sp,
+                                hipStream_t s) {
   if (T == 0) return hipSuccess;
   const int64_t want = (T + 3) / 4;
   const int blocks = (int)(want < 8192 ? want : 8192);
   if (dtype == 0)
-    router_bwd_dx_kernel<bf16_t><<<blocks, 256, 0, s>>>((const bf16_t*)Wr, idx, gates, dgates, T, h, E, k, EP, accumulate, with_dx, (bf16_t*)dX, (bf16_t*)D);
+    router_bwd_dx_kernel<bf16_t><<<blocks, 256, 0, s>>>((const bf16_t*)Wr, idx, gates, dgates, T, h, E,
+                                                        k, EP, accumulate, (bf16_t*)dX, (bf16_t*)D, sp);
   else
-    router_bwd_dx_kernel<float><<<blocks, 256, 0, s>>>((const float*)Wr, idx, gates, dgates, T, h, E, k, EP, accumulate, with_dx, (float*)dX, (float*)D);
-  return hipGetLastError();
-}
-
-hipError_t launch_router_split_meta(int32_t* offsets, int32_t* order, int32_t* tok, int64_t T, int S,
-                                    hipStream_t s) {
-  split_offsets_kernel<<<(S + 1 + 255) / 256, 256, 0, s>>>(offsets, order, T, S);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || T == 0) return e;
-  iota_kernel<<<(int)((T + 255) / 256), 256, 0, s>>>(tok, (int)T);
+    router_bwd_dx_kernel<float><<<blocks, 256, 0, s>>>((const float*)Wr, idx, gates, dgates, T, h, E,
+                                                       k, EP, accumulate, (float*)dX, (float*)D, sp);
   return hipGetLastError();
 }
 

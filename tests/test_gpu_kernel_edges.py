@@ -102,3 +102,71 @@ def test_f32_tile_shape_by_grid(mf, T):
     assert relerr(Y, om.moe_fwd(case["X"], case["idx"], case["gates"], case["W1"], case["W2"],
                                 1)) <= TOL["f32"]
     _check_bwd(mf, w, 40 + T, 1, False)
+
+
+# Router: both sides of the logits GEMM's tile rules (one round of 64-row, then
+# of 128-row tiles), the dz rows' 64-token workgroups, and routers too small
+# for a whole tile.  T = 1 and 65 also at 96 logits (dX from the dz kernel's
+# per-token form).
+@pytest.mark.parametrize("T,E,k", [(1, 256, 8), (65, 96, 3), (65, 128, 16), (16384, 256, 2),
+                                   (16385, 256, 2), (32768, 256, 4), (32769, 256, 4)])
+def test_router_tile_rules(mf, T, E, k):
+    from oracle import router as orr
+    t = torch()
+    h = 64
+    log(f"router rules T={T} E={E} k={k}")
+    rng = np.random.default_rng(T + E)
+    X = mw.round_to_bf16(rng.standard_normal((T, h)))
+    Wr = mw.round_to_bf16(rng.standard_normal((E, h)) / 8)
+    dg = rng.standard_normal((T, k)).astype(np.float32)
+    Xd, Wd = (t.from_numpy(a).cuda().bfloat16() for a in (X, Wr))
+    s = mf.make_shape(T, h, 64, E, k, mf.BF16)
+    idx = t.full((T, k), -1, dtype=t.int32, device="cuda")
+    gates, logits = t.empty((T, k), device="cuda"), t.empty((T, E), device="cuda")
+    mf.memfine_router_fwd(s, Xd, Wd, idx, gates, logits)
+    lg = host(logits)
+    assert relerr(lg, orr.logits_of(X, Wr)) <= 1e-5      # fp32 sums of exact products
+    ref = orr.router_fwd(X, Wr, k, logits=lg)
+    assert np.array_equal(idx.cpu().numpy(), ref["idx"])
+    assert np.max(np.abs(host(gates) - ref["gates"])) <= 1e-5
+    dX, dWr = t.empty((T, h), device="cuda").bfloat16(), t.empty((E, h), device="cuda")
+    mf.memfine_router_bwd(s, Xd, Wd, idx, gates, t.from_numpy(dg).cuda(), dX, dWr)
+    R = orr.router_bwd(X, Wr, ref["idx"], lg, dg)
+    assert relerr(host(dX), R["dX"]) <= TOL["bf16"]
+    assert relerr(host(dWr), R["dWr"]) <= TOL["bf16"]
+
+
+# The top-k of wide routers on logits that tie (+0 and -0 among them), are
+# infinite, or are not numbers (never selected): X is one-hot, so a token's
+# logits are a column of Wr.
+@pytest.mark.parametrize("E", [96, 100, 256])
+def test_router_topk_special_logits(mf, E):
+    t = torch()
+    h, k = 64, 6
+    log(f"router top-k special E={E}")
+    rng = np.random.default_rng(E)
+    cols = rng.integers(-2, 3, size=(h, E)).astype(np.float32)   # many ties
+    cols[cols == 0] = np.where(rng.random((cols == 0).sum()) < 0.5, 0.0, -0.0)
+    Wr = np.ascontiguousarray(cols.T)
+    X = np.eye(h, dtype=np.float32)
+    s = mf.make_shape(h, h, 64, E, k, mf.BF16)
+    idx = t.empty((h, k), dtype=t.int32, device="cuda")
+    gates, logits = t.empty((h, k), device="cuda"), t.empty((h, E), device="cuda")
+    mf.memfine_router_fwd(s, t.from_numpy(X).cuda().bfloat16(),
+                          t.from_numpy(Wr).cuda().bfloat16(), idx, gates, logits)
+    lg, sel = host(logits).astype(np.float64), idx.cpu().numpy()
+    assert np.array_equal(lg, cols.astype(np.float64))
+    order = np.lexsort((np.broadcast_to(np.arange(E), lg.shape), -lg), axis=-1)[:, :k]
+    assert np.array_equal(sel, order)
+    # expert 1 at +inf, 2 not a number, 5 at -inf, the others falling with the id
+    X2 = np.ones((4, h), np.float32)
+    Wr2 = np.zeros((E, h), np.float32)
+    Wr2[:, 0] = -np.arange(E) / 8.0
+    Wr2[2, 1] = np.nan
+    Wr2[5, 1] = -np.inf
+    Wr2[1, 1] = np.inf
+    s = mf.make_shape(4, h, 64, E, k, mf.BF16)
+    idx, gates = t.empty((4, k), dtype=t.int32, device="cuda"), t.empty((4, k), device="cuda")
+    mf.memfine_router_fwd(s, t.from_numpy(X2).cuda().bfloat16(),
+                          t.from_numpy(Wr2).cuda().bfloat16(), idx, gates)
+    assert idx.cpu().numpy().tolist() == [[1, 0, 3, 4, 6, 7]] * 4
