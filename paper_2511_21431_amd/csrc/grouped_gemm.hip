@@ -2094,8 +2094,14 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
 // small tiles over the CUs and bytes in flight (Thin: 32 KB of weights per
 // workgroup ahead); many rows want operand reuse (256 x 256, one per CU).
 constexpr int kThinRows = 48, kMidRows = 320;
-// The weight gradients take 256 x 256 tiles unless the grid is too small to
-// give most CUs one.
+// The weight gradients (K = an expert's rows) take 256 x 256 tiles from 640 of
+// them (2.5 rounds of the CUs): below, the launch lasts as long as the tiles
+// of the expert with most rows, and 128 x 128 tiles spread them over four
+// times the workgroups.  Measured, 256 x 256 against 128 x 128: 256 tiles (32
+// experts, 512 x 1024, 1500 rows) 186 / 110 us, 512 tiles (8, 1024 x 4096,
+// 1000 rows) 120 / 98, 560 (20, 1600 x 960, 375 rows) 70 / 51, 768 (16, 2048
+// x 1408, 512 rows) 82 / 92, 1024 (8, 8192 x 1024, 1000 rows) 184 / 231.
+constexpr int kWgradGrid = 640;
 //
 // fp32: 64-row tiles up to kF32SmallGrid 128 x 128 tiles (2.5 rounds of the
 // 512 that are resident): 36 m-tiles x 8 (FC1 dgrad at 4096 slots, h 1024, F
@@ -2128,7 +2134,9 @@ hipError_t launch_auto(const GemmArgs& g_in, hipStream_t s) {
     if (g.n <= (int64_t)kThinRows * g.E) return launch_walk<bf16_t, PT, Thin>(g, s);
     if (g.n < (int64_t)kMidRows * g.E) return launch_walk<bf16_t, PT, Small>(g, s);
   }
-  if (Any::grid(g) >= 128) {
+  // (tile_ctr: the layer's weight gradients; the router's have equal row ranges)
+  const int least = !Any::kEqualTiles && g.tile_ctr != nullptr ? kWgradGrid : 128;
+  if (Any::grid(g) >= least) {
     if (g.split_tail) return launch_split_cfg<PT, Big8, Quarter8>(g, s);
     return launch_tiles<bf16_t, PT, Big8>(g, s);
   }

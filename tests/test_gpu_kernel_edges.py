@@ -90,6 +90,17 @@ def test_tile_shape_by_rows(mf, T, E, h, F):
             assert np.array_equal(other[key], B[key]), (tile, key)
 
 
+# Weight gradients: 128 x 128 tiles below a grid of 640 tiles of 256 x 256 (here
+# one per expert), the larger ones from there; most experts have no row.
+@pytest.mark.parametrize("E", [639, 640])
+def test_wgrad_tile_shape_by_grid(mf, E):
+    w = mw.Workload("wgrid", T=777, h=64, F=64, E=E, k=2, dtype="bf16", routing="dirichlet",
+                    alpha=0.3)
+    log(f"wgrad tile shape E={E}")
+    for accumulate in (False, True):
+        _check_bwd(mf, w, 70 + E, 2, accumulate)
+
+
 # fp32: 64-row tiles below 1280 tiles of 128 x 128, the larger ones from there
 # (FC1: F / 64 = 256 column tiles x 4 and x 5 row tiles).
 @pytest.mark.parametrize("T", [512, 640])
