@@ -122,7 +122,7 @@ typedef struct memfine_plan_info {
 /*
  * Launch options, for measurements and tests.  Every GEMM setting (tile,
  * raster, split_tail, pair, streams) gives bit-identical results (each
- * output element is one lane's fp32 sum in increasing K order whatever the
+ * output element is one lane's fp32 sum in one fixed K order whatever the
  * tiling); chunk_order changes the order of the sums that form Y and dX.
  * Process-wide; a layer call reads them once when it starts, and
  * memfine_workspace_bytes (hence memfine_plan) follows chunk_order.

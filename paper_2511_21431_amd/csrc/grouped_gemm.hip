@@ -219,19 +219,26 @@ __device__ __forceinline__ u32x2_t pack4(const float (&f)[4]) {
   return x;
 }
 
+// One K step: kKStep values of K per operand row, kSub MFMAs per block.  fp32
+// takes 8 values as 4 instructions of 2: lane half hh holds k = 4 hh .. 4 hh +
+// 3 of the step, so that instruction s multiplies k = s and 4 + s and a
+// K-contiguous operand is one 16-byte LDS read per step (one 4-byte read per
+// instruction, 32 rows on 16 banks, kept the LDS as busy as the matrix cores
+// on 32 x 32 wave tiles: FC2 at 4096 slots, h 1024, F 1408 149 -> 129 us, FC1
+// 237 -> 223 us).
 template <typename T> struct Mma;
 template <> struct Mma<bf16_t> {
-  static constexpr int kKStep = 16;
+  static constexpr int kKStep = 16, kSub = 1;
   typedef bf16x8_t Frag;
-  __device__ __forceinline__ static void mma(const Frag& a, const Frag& b, f32x16_t& c) {
+  __device__ __forceinline__ static void mma(const Frag& a, const Frag& b, f32x16_t& c, int) {
     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
 };
 template <> struct Mma<float> {
-  static constexpr int kKStep = 2;
-  typedef float Frag;
-  __device__ __forceinline__ static void mma(const Frag& a, const Frag& b, f32x16_t& c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  static constexpr int kKStep = 8, kSub = 4;
+  typedef f32x4_t Frag;
+  __device__ __forceinline__ static void mma(const Frag& a, const Frag& b, f32x16_t& c, int s) {
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], c, 0, 0, 0);
   }
 };
 
@@ -254,10 +261,9 @@ __device__ __forceinline__ bf16x8_t kc_read_bf16(const char* lds, int row0, int 
   return *(const bf16x8_t*)(lds + kc_off<KB>(row, kk * 2 + (lane >> 5)));
 }
 template <int KB, int ROWS>
-__device__ __forceinline__ float kc_read_f32(const char* lds, int row0, int kk, int lane) {
+__device__ __forceinline__ f32x4_t kc_read_f32(const char* lds, int row0, int kk, int lane) {
   const int row = row0 + (lane & 31);
-  const int kel = kk * 2 + (lane >> 5);
-  return *(const float*)(lds + kc_off<KB>(row, kel >> 2) + ((kel & 3) << 2));
+  return *(const f32x4_t*)(lds + kc_off<KB>(row, kk * 2 + (lane >> 5)));
 }
 
 template <typename T, int ROWS, int NW, int KB, bool DIRECT> struct KcOp {
@@ -308,16 +314,18 @@ template <typename T, int ROWS, int NW, int KB, bool DIRECT> struct KcOp {
 
 // ------------------------------------------------------------ K-strided
 // LDS tile: BK rows (one per k) of ROWS elements (pitch P = ROWS * size);
-// 16-byte unit u of k-row k sits at unit u ^ ks_sw(k).  The swizzle spreads
-// the 4 consecutive k-rows that one transposing read touches over distinct
-// banks.  A copy instruction writes 1 KB = 1024 / P whole k-rows.
-__device__ __forceinline__ int ks_sw(int k) {
+// 16-byte unit u of k-row k sits at unit u ^ ks_sw(k).  bf16: the swizzle
+// spreads the 4 consecutive k-rows that one transposing read touches over
+// distinct banks; fp32: the k-rows of the two lane halves, 4 apart, each 128
+// bytes.  A copy instruction writes 1 KB = 1024 / P whole k-rows.
+template <int ES> __device__ __forceinline__ int ks_sw(int k) {
+  if constexpr (ES == 4) return (k & 4) * 2;
   // k & 3 = 0, 1, 2, 3  ->  units 0, 10, 4, 14 (branch-free)
-  return ((k & 1) * 10) ^ ((k & 2) * 2);
+  else return ((k & 1) * 10) ^ ((k & 2) * 2);
 }
 
 template <typename T, int ROWS, int NW, int KB, bool DIRECT> struct KsOp {
-  static constexpr int kReadsPerFrag = sizeof(T) == 2 ? 2 : 1;
+  static constexpr int kReadsPerFrag = sizeof(T) == 2 ? 2 : 4;
   static constexpr int BKE = KB / (int)sizeof(T);  // k-rows per K tile
   static constexpr int P = ROWS * (int)sizeof(T);
   static constexpr int KPI = 1024 / P;          // k-rows per copy instruction
@@ -336,7 +344,7 @@ template <typename T, int ROWS, int NW, int KB, bool DIRECT> struct KsOp {
   __device__ __forceinline__ static int col_of(int i, int wave, int lane) {
     const int k = k_of(i, wave, lane);
     const int p = ((lane * 16) % P) >> 4;
-    return (DIRECT ? (p ^ ks_sw(k)) : p) * V;
+    return (DIRECT ? (p ^ ks_sw<(int)sizeof(T)>(k)) : p) * V;
   }
   __device__ __forceinline__ void issue(char* lds, uint32_t soff, int wave) {
 #pragma clang loop unroll(full)
@@ -351,13 +359,13 @@ template <typename T, int ROWS, int NW, int KB, bool DIRECT> struct KsOp {
 #pragma clang loop unroll(full)
       for (int i = 0; i < I; ++i) {
         const int k = k_of(i, wave, lane);
-        *(u32x4_t*)(lds + k * P + ((p ^ ks_sw(k)) << 4)) = stage[i];
+        *(u32x4_t*)(lds + k * P + ((p ^ ks_sw<(int)sizeof(T)>(k)) << 4)) = stage[i];
       }
     }
   }
   __device__ __forceinline__ static int phys(int k, int col) {  // byte of element col in k-row
     const int b = col * (int)sizeof(T);
-    return k * P + ((((b >> 4) ^ ks_sw(k))) << 4) + (b & 15);
+    return k * P + ((((b >> 4) ^ ks_sw<(int)sizeof(T)>(k))) << 4) + (b & 15);
   }
   __device__ __forceinline__ static typename Mma<T>::Frag read(const char* lds, int col0, int kk,
                                                                int lane);
@@ -366,7 +374,7 @@ template <typename T, int ROWS, int NW, int KB, bool DIRECT> struct KsOp {
 template <int P, int ES>
 __device__ __forceinline__ int ks_phys(int k, int col) {
   const int b = col * ES;
-  return k * P + ((((b >> 4) ^ ks_sw(k))) << 4) + (b & 15);
+  return k * P + ((((b >> 4) ^ ks_sw<ES>(k))) << 4) + (b & 15);
 }
 // `lds` is restrict: inlined, the transposing reads then carry alias-scope
 // information, without which the compiler makes every LDS read wait for all
@@ -390,8 +398,12 @@ __device__ __forceinline__ bf16x8_t ks_read_bf16(const char* __restrict__ lds, i
   return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 template <int ROWS>
-__device__ __forceinline__ float ks_read_f32(const char* lds, int col0, int kk, int lane) {
-  return *(const float*)(lds + ks_phys<ROWS * 4, 4>(kk * 2 + (lane >> 5), col0 + (lane & 31)));
+__device__ __forceinline__ f32x4_t ks_read_f32(const char* lds, int col0, int kk, int lane) {
+  f32x4_t x;
+#pragma clang loop unroll(full)
+  for (int s = 0; s < 4; ++s)
+    x[s] = *(const float*)(lds + ks_phys<ROWS * 4, 4>(kk * 8 + (lane >> 5) * 4 + s, col0 + (lane & 31)));
+  return x;
 }
 template <typename T, int ROWS, int NW, int KB, bool DIRECT>
 __device__ __forceinline__ typename Mma<T>::Frag KsOp<T, ROWS, NW, KB, DIRECT>::read(const char* lds, int col0,
@@ -419,9 +431,20 @@ template <class C> __device__ __forceinline__ void zero_acc(Accum<C>& acc) {
 // either way.
 template <typename T, bool kRowsInRegs>
 __device__ __forceinline__ void mma_block(const typename Mma<T>::Frag& a,
-                                          const typename Mma<T>::Frag& b, f32x16_t& c) {
-  if constexpr (kRowsInRegs) Mma<T>::mma(a, b, c);
-  else Mma<T>::mma(b, a, c);
+                                          const typename Mma<T>::Frag& b, f32x16_t& c, int s) {
+  if constexpr (kRowsInRegs) Mma<T>::mma(a, b, c, s);
+  else Mma<T>::mma(b, a, c, s);
+}
+// All blocks' MFMAs of one K step.
+template <typename T, class C, bool kRowsInRegs>
+__device__ __forceinline__ void mma_step(const typename Mma<T>::Frag (&a)[C::MB],
+                                         const typename Mma<T>::Frag (&b)[C::NB], Accum<C>& acc) {
+#pragma clang loop unroll(full)
+  for (int s = 0; s < Mma<T>::kSub; ++s)
+#pragma clang loop unroll(full)
+    for (int i = 0; i < C::MB; ++i)
+#pragma clang loop unroll(full)
+      for (int j = 0; j < C::NB; ++j) mma_block<T, kRowsInRegs>(a[i], b[j], acc.v[i][j], s);
 }
 
 // One K tile: the operand fragments of K step kk+1 are read from LDS while
@@ -433,7 +456,7 @@ __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C
                                          int wn, int lane) {
   constexpr int KS = C::KB / (int)sizeof(T) / Mma<T>::kKStep;
   constexpr int kReads = OA::kReadsPerFrag * C::MB + OB::kReadsPerFrag * C::NB;
-  constexpr int kMfma = C::MB * C::NB;
+  constexpr int kMfma = C::MB * C::NB * Mma<T>::kSub;
   typename Mma<T>::Frag a[2][C::MB], b[2][C::NB];
   constexpr int kPrio = C::DIRECT ? 0 : kMmaPrio;
   if constexpr (kPrio > 0) __builtin_amdgcn_s_setprio(kPrio);
@@ -452,11 +475,7 @@ __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C
 #pragma clang loop unroll(full)
       for (int i = 0; i < C::MB; ++i) a[nx][i] = OA::read(As, wm * C::WTM + i * 32, kk + 1, lane);
     }
-#pragma clang loop unroll(full)
-    for (int i = 0; i < C::MB; ++i)
-#pragma clang loop unroll(full)
-      for (int j = 0; j < C::NB; ++j)
-        mma_block<T, kRowsInRegs>(a[cu][i], b[cu][j], acc.v[i][j]);
+    mma_step<T, C, kRowsInRegs>(a[cu], b[cu], acc);
   }
   if constexpr (kSchedHints) {
     // DS reads of step 0, then per step: MFMAs of step kk interleaved with the
@@ -496,7 +515,7 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
   constexpr int KS = C::KB / (int)sizeof(T) / Mma<T>::kKStep;
   static_assert(KS % 2 == 0, "the carried step uses fragment set 1");
   constexpr int kReads = OA::kReadsPerFrag * C::MB + OB::kReadsPerFrag * C::NB;
-  constexpr int kMfma = C::MB * C::NB;
+  constexpr int kMfma = C::MB * C::NB * Mma<T>::kSub;
   constexpr int kPrio = C::DIRECT ? 0 : kMmaPrio;  // as in mma_tile
   if constexpr (kPrio > 0) __builtin_amdgcn_s_setprio(kPrio);
 #pragma clang loop unroll(full)
@@ -504,11 +523,7 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
 #pragma clang loop unroll(full)
   for (int j = 0; j < C::NB; ++j) f.b[0][j] = OB::read(Bs, wn * C::WTN + j * 32, 0, lane);
   if constexpr (kCarry) {
-#pragma clang loop unroll(full)
-    for (int i = 0; i < C::MB; ++i)
-#pragma clang loop unroll(full)
-      for (int j = 0; j < C::NB; ++j)
-        mma_block<T, kRowsInRegs>(f.a[1][i], f.b[1][j], acc.v[i][j]);
+    mma_step<T, C, kRowsInRegs>(f.a[1], f.b[1], acc);
   }
 #pragma clang loop unroll(full)
   for (int kk = 0; kk + 1 < KS; ++kk) {
@@ -518,11 +533,7 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
     for (int j = 0; j < C::NB; ++j) f.b[nx][j] = OB::read(Bs, wn * C::WTN + j * 32, kk + 1, lane);
 #pragma clang loop unroll(full)
     for (int i = 0; i < C::MB; ++i) f.a[nx][i] = OA::read(As, wm * C::WTM + i * 32, kk + 1, lane);
-#pragma clang loop unroll(full)
-    for (int i = 0; i < C::MB; ++i)
-#pragma clang loop unroll(full)
-      for (int j = 0; j < C::NB; ++j)
-        mma_block<T, kRowsInRegs>(f.a[cu][i], f.b[cu][j], acc.v[i][j]);
+    mma_step<T, C, kRowsInRegs>(f.a[cu], f.b[cu], acc);
   }
   if constexpr (kSchedHints) {
     // the carried MFMAs interleaved with step 0's reads, then per step the
@@ -552,10 +563,7 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
 }
 template <typename T, class C, bool kRowsInRegs>
 __device__ __forceinline__ void mma_flush(Accum<C>& acc, const FragSets<T, C>& f) {
-#pragma clang loop unroll(full)
-  for (int i = 0; i < C::MB; ++i)
-#pragma clang loop unroll(full)
-    for (int j = 0; j < C::NB; ++j) mma_block<T, kRowsInRegs>(f.a[1][i], f.b[1][j], acc.v[i][j]);
+  mma_step<T, C, kRowsInRegs>(f.a[1], f.b[1], acc);
 }
 
 // Accumulator layout (kRowsInRegs false).  The MFMA is given the B fragment first,
