@@ -59,6 +59,7 @@ namespace {
 
 
 constexpr uint32_t kOOB = 0x80000000u;    // byte offset past every buffer's range
+constexpr int kNonTemporal = 2;           // cache policy of a buffer access: nt
 #ifndef MEMFINE_SCHED_HINTS
 #define MEMFINE_SCHED_HINTS 1
 #endif
@@ -424,19 +425,8 @@ template <class C> __device__ __forceinline__ void zero_acc(Accum<C>& acc) {
       for (int q = 0; q < 16; ++q) acc.v[i][j][q] = 0.f;
 }
 
-// Operand order of the product (P::kRowsInRegs).  false: the MFMA gets the B
-// fragment first, so a lane of the accumulator block holds one output row and
-// runs of consecutive columns; true: A first, a lane holds one output column
-// and the block's rows lie in its registers.  Each element is the same sum
-// either way.
-template <typename T, bool kRowsInRegs>
-__device__ __forceinline__ void mma_block(const typename Mma<T>::Frag& a,
-                                          const typename Mma<T>::Frag& b, f32x16_t& c, int s) {
-  if constexpr (kRowsInRegs) Mma<T>::mma(a, b, c, s);
-  else Mma<T>::mma(b, a, c, s);
-}
 // All blocks' MFMAs of one K step.
-template <typename T, class C, bool kRowsInRegs>
+template <typename T, class C>
 __device__ __forceinline__ void mma_step(const typename Mma<T>::Frag (&a)[C::MB],
                                          const typename Mma<T>::Frag (&b)[C::NB], Accum<C>& acc) {
 #pragma clang loop unroll(full)
@@ -444,14 +434,14 @@ __device__ __forceinline__ void mma_step(const typename Mma<T>::Frag (&a)[C::MB]
 #pragma clang loop unroll(full)
     for (int i = 0; i < C::MB; ++i)
 #pragma clang loop unroll(full)
-      for (int j = 0; j < C::NB; ++j) mma_block<T, kRowsInRegs>(a[i], b[j], acc.v[i][j], s);
+      for (int j = 0; j < C::NB; ++j) Mma<T>::mma(b[j], a[i], acc.v[i][j], s);
 }
 
 // One K tile: the operand fragments of K step kk+1 are read from LDS while
 // the MFMAs of step kk run (two fragment register sets); scheduling
 // barriers interleave the LDS reads with the MFMAs so that neither waits
 // on the other.
-template <typename T, class C, class OA, class OB, bool kRowsInRegs = false>
+template <typename T, class C, class OA, class OB>
 __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C>& acc, int wm,
                                          int wn, int lane) {
   constexpr int KS = C::KB / (int)sizeof(T) / Mma<T>::kKStep;
@@ -475,7 +465,7 @@ __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C
 #pragma clang loop unroll(full)
       for (int i = 0; i < C::MB; ++i) a[nx][i] = OA::read(As, wm * C::WTM + i * 32, kk + 1, lane);
     }
-    mma_step<T, C, kRowsInRegs>(a[cu], b[cu], acc);
+    mma_step<T, C>(a[cu], b[cu], acc);
   }
   if constexpr (kSchedHints) {
     // DS reads of step 0, then per step: MFMAs of step kk interleaved with the
@@ -509,7 +499,7 @@ __device__ __forceinline__ void mma_tile(const char* As, const char* Bs, Accum<C
 template <typename T, class C> struct FragSets {
   typename Mma<T>::Frag a[2][C::MB], b[2][C::NB];
 };
-template <typename T, class C, class OA, class OB, bool kCarry, bool kRowsInRegs>
+template <typename T, class C, class OA, class OB, bool kCarry>
 __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, Accum<C>& acc, int wm,
                                                int wn, int lane, FragSets<T, C>& f) {
   constexpr int KS = C::KB / (int)sizeof(T) / Mma<T>::kKStep;
@@ -523,7 +513,7 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
 #pragma clang loop unroll(full)
   for (int j = 0; j < C::NB; ++j) f.b[0][j] = OB::read(Bs, wn * C::WTN + j * 32, 0, lane);
   if constexpr (kCarry) {
-    mma_step<T, C, kRowsInRegs>(f.a[1], f.b[1], acc);
+    mma_step<T, C>(f.a[1], f.b[1], acc);
   }
 #pragma clang loop unroll(full)
   for (int kk = 0; kk + 1 < KS; ++kk) {
@@ -533,7 +523,7 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
     for (int j = 0; j < C::NB; ++j) f.b[nx][j] = OB::read(Bs, wn * C::WTN + j * 32, kk + 1, lane);
 #pragma clang loop unroll(full)
     for (int i = 0; i < C::MB; ++i) f.a[nx][i] = OA::read(As, wm * C::WTM + i * 32, kk + 1, lane);
-    mma_step<T, C, kRowsInRegs>(f.a[cu], f.b[cu], acc);
+    mma_step<T, C>(f.a[cu], f.b[cu], acc);
   }
   if constexpr (kSchedHints) {
     // the carried MFMAs interleaved with step 0's reads, then per step the
@@ -561,12 +551,12 @@ __device__ __forceinline__ void mma_tile_carry(const char* As, const char* Bs, A
   }
   if constexpr (kPrio > 0) __builtin_amdgcn_s_setprio(0);
 }
-template <typename T, class C, bool kRowsInRegs>
+template <typename T, class C>
 __device__ __forceinline__ void mma_flush(Accum<C>& acc, const FragSets<T, C>& f) {
-  mma_step<T, C, kRowsInRegs>(f.a[1], f.b[1], acc);
+  mma_step<T, C>(f.a[1], f.b[1], acc);
 }
 
-// Accumulator layout (kRowsInRegs false).  The MFMA is given the B fragment first,
+// Accumulator layout.  The MFMA is given the B fragment as its first operand,
 // so block (mb, nb) holds the transposed product: element q of a lane sits at
 // tile row acc_row(wm, mb, lane) and tile column acc_col(wn, nb, q / 4, lane)
 // + q % 4.  Each lane thus owns one output row and four runs of four
@@ -1288,8 +1278,8 @@ template <typename T, class C> struct ProbFC1Dgrad {
 template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
   static constexpr int kRaster = 0;  // preferred tile order: tile ids in order (no XCD blocks)
   static constexpr bool kEqualTiles = false;  // K = the expert's rows
-  static constexpr bool kEpilogueLoads = false;  // no stage slab; the next tile's copies
-  // go out before the epilogue (its loads of the old dW, when adding, then wait behind them)
+  static constexpr bool kEpilogueLoads = false;  // the next tile's copies go out before the
+  // epilogue (its loads of the old dW, when adding, then wait behind them)
   typedef KsOp<T, C::BM, C::NW, C::KB, C::DA> OA;
   typedef KsOp<T, C::BN, C::NW, C::KB, C::DB> OB;
   static constexpr int IG = kFC1 ? OB::I : OA::I;  // copy instructions of the gathered operand
@@ -1484,23 +1474,29 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
       for (int i = 0; i < IG; ++i) tok[d][i] = tok[d + 1][i];
     load_tokens(kt + D, wave, lane, tok[D - 1]);  // D tiles ahead
   }
-  // The block's rows lie in registers (mma_block), so that one 4-byte store
-  // (load) instruction covers 128 contiguous bytes of each of two rows.  The
-  // epilogue is bound by the requests that reach the L2 and, when adding, by
-  // the latency of the old values: with a lane holding 4 columns of a row, a
-  // 16-byte store touched 32 rows in 32-byte pieces, four times the requests,
-  // and each block of 32 rows waited for its own loads; now the loads run two
-  // blocks ahead.  FC1 wgrad at 16384 slots, 32 experts, h 7168, F 2048:
-  // adding 2.36 -> 1.87 ms, writing 1.62 -> 1.46 ms (3.76 GB of dW1 read and
-  // written at the copy rate: 1.45 ms); at 131072 slots 7.60 -> 7.21 ms.
-  static constexpr bool kRowsInRegs = true;
   // Vector-memory stores epilogue() issues: every one, whatever the tile's
   // extent (elements outside it get an offset past the range).  When it adds
   // into dW it also loads the old values and waits for them, so the loads
   // are retired, with everything issued before them, when it returns.
-  static constexpr int kEpiStores = C::MB * C::NB * 16;
+  static constexpr int kEpiStores = C::MB * C::NB * 4;
+  // Each 32 x 32 block of the wave goes through its LDS slab (32 rows of 128
+  // bytes, 16-byte units XOR-swizzled by row), so that a 16-byte access covers 8
+  // rows x 128 contiguous bytes; when adding, the old values of the next two
+  // blocks are in flight.  dW is read and written once per launch: non-temporal
+  // accesses keep it from displacing the operands that other tiles and the
+  // next kernels read.  (Straight from the accumulators, 16-byte accesses
+  // touch 32 rows in 32-byte pieces: four times the L2 requests, and non-
+  // temporal ones would send partial lines to memory.)  The launch is bound by
+  // memory where the experts have few rows: FC1 wgrad at 16384 slots, 32
+  // experts, h 7168, F 2048: adding 2.36 (from the accumulators) -> 1.88 (whole
+  // lines, cached) -> 1.79 ms, 3.76 GB read and written; overwriting 1.62 -> 1.43
+  // -> 1.33; at 131072 slots adding 7.60 -> 7.23.
   __device__ __forceinline__ void epilogue(const GemmArgs& g, const Tile& t, const Accum<C>& acc,
-                                           int wm, int wn, int lane, char* slab) const {
+                                           int wm, int wn, int, char* slab) const {
+    // the lane index anew and opaque: offsets derived from it would otherwise be
+    // kept in registers over the next tile's K loop, which has none to spare
+    int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(lane));
     const int Nn = N(g);  // % 64 == 0 and M % 32 == 0: a 32 x 32 block is all in or all out
     const uint32_t rowb = (uint32_t)Nn * sizeof(float);
     // the tile is the workgroup's: its fields are uniform, which the compiler
@@ -1514,34 +1510,47 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
                   (int64_t)mrows * rowb);
     const bool add = acc_of(t);
     constexpr int U = C::MB * C::NB, D = U < 3 ? U : 3;  // blocks; blocks of old values in flight
-    // Lane l of block u: column l % 32, rows 8 gq + 4 (l / 32) + c.  The lane's
-    // offset is fixed, the row goes in the scalar offset.
-    const uint32_t lane_off = (uint32_t)(lane & 31) * 4 + (uint32_t)(lane >> 5) * 4 * rowb;
+    // Access q of block u: lane l has 16 bytes at unit l % 8 of row 8 q + l / 8.
+    // The lane's offset is fixed, block and row group go in the scalar offset.
+    const uint32_t lane_off = (uint32_t)(lane >> 3) * rowb + (uint32_t)(lane & 7) * 16;
     auto voff = [&](int u) {
       const int mb = u / C::NB, nb = u % C::NB;
-      const int col = n0 + wn * C::WTN + nb * 32;
-      return wm * C::WTM + mb * 32 < mrows && col < Nn ? lane_off + (uint32_t)col * 4 : kOOB;
+      return wm * C::WTM + mb * 32 < mrows && n0 + wn * C::WTN + nb * 32 < Nn ? lane_off : kOOB;
     };
     auto soff = [&](int u, int q) {
-      return (uint32_t)(wm * C::WTM + (u / C::NB) * 32 + 8 * (q >> 2) + (q & 3)) * rowb;
+      return (uint32_t)(wm * C::WTM + (u / C::NB) * 32 + 8 * q) * rowb +
+             (uint32_t)(n0 + wn * C::WTN + (u % C::NB) * 32) * 4;
     };
-    float old[D][16];
+    u32x4_t old[D][4];
     auto fetch = [&](int u) {
       const uint32_t vo = voff(u);
 #pragma clang loop unroll(full)
-      for (int q = 0; q < 16; ++q)
-        old[u % D][q] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, soff(u, q), 0));
+      for (int q = 0; q < 4; ++q)
+        old[u % D][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, soff(u, q), kNonTemporal);
     };
+    const int wr = (lane & 31) * 128 + (((lane >> 5) ^ (lane & 7)) << 4);
+    const int rd = (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) << 4);
     auto put = [&](int u, bool added) {
+#pragma clang loop unroll(full)
+      for (int gq = 0; gq < 4; ++gq) {  // columns 8 gq + 4 (l / 32): unit 2 gq + l / 32
+        float v[4];
+        acc_run(acc.v[u / C::NB][u % C::NB], gq, v);
+        *(f32x4_t*)(slab + (wr ^ (gq << 5))) = (f32x4_t){v[0], v[1], v[2], v[3]};
+      }
+      asm volatile("" ::: "memory");  // the writes above before the reads below
       const uint32_t vo = voff(u);
 #pragma clang loop unroll(full)
-      for (int q = 0; q < 16; ++q) {
-        float v = acc.v[u / C::NB][u % C::NB][q];
-        if (added) v += old[u % D][q];
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, vo, soff(u, q),
-                                              0);
+      for (int q = 0; q < 4; ++q) {
+        f32x4_t x = *(const f32x4_t*)(slab + rd + q * 1024);
+        if (added) {
+          const f32x4_t o = __builtin_bit_cast(f32x4_t, old[u % D][q]);
+#pragma clang loop unroll(full)
+          for (int c = 0; c < 4; ++c) x[c] += o[c];
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), rs, vo, soff(u, q),
+                                               kNonTemporal);
       }
+      asm volatile("" ::: "memory");  // the reads above before the next writes
     };
     if (add) {
 #pragma clang loop unroll(full)
@@ -1573,11 +1582,6 @@ template <int N> __device__ __forceinline__ void wait_vm() {
 // with tile kt-1, whose stage the next copy overwrites.
 struct NoNext {
   __device__ __forceinline__ void operator()(char*, int, int) const {}
-};
-// Problems whose accumulators hold output rows in registers (mma_block).
-template <class P, class = void> struct RowsInRegs { static constexpr bool value = false; };
-template <class P> struct RowsInRegs<P, decltype((void)P::kRowsInRegs)> {
-  static constexpr bool value = P::kRowsInRegs;
 };
 // Problems whose tile columns pair gate and up rows inside a wave (FC1).
 template <class P, class = void> struct PairedColumns { static constexpr bool value = false; };
@@ -1658,7 +1662,6 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
   if (!prefetched) p.init(g, t, w, lane);
   Accum<C> acc;
   p.init_acc(g, t, acc, wm, wn, lane);
-  constexpr bool kRows = RowsInRegs<P>::value;
   constexpr int kCopies = P::OA::I + P::OB::I;  // copy instructions per wave per K tile
   const int nk = k_tiles<T, C>(t);
   if constexpr (C::DIRECT) {
@@ -1692,19 +1695,19 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
       if constexpr (kCarryStep) {
         if (active) {
           if (kt == 0)
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, false, kRows>(
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, false>(
                 cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
           else
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, true, kRows>(
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, true>(
                 cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
         }
       } else {
         if (active)
-          mma_tile<T, C, typename P::OA, typename P::OB, kRows>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
+          mma_tile<T, C, typename P::OA, typename P::OB>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
       }
     }
     if constexpr (kCarryStep)
-      if (active && nk > 0) mma_flush<T, C, kRows>(acc, fr);
+      if (active && nk > 0) mma_flush<T, C>(acc, fr);
   } else {
     // Register-staged double buffer: the loads of tile kt + 1 are in flight
     // while tile kt is multiplied, then written to the stage that tile kt - 1
@@ -1726,15 +1729,15 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
       if constexpr (kCarryStep) {
         if (active) {
           if (kt == 0)
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, false, kRows>(
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, false>(
                 cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
           else
-            mma_tile_carry<T, C, typename P::OA, typename P::OB, true, kRows>(
+            mma_tile_carry<T, C, typename P::OA, typename P::OB, true>(
                 cur, cur + C::BM * C::KB, acc, wm, wn, lane, fr);
         }
       } else {
         if (active)
-          mma_tile<T, C, typename P::OA, typename P::OB, kRows>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
+          mma_tile<T, C, typename P::OA, typename P::OB>(cur, cur + C::BM * C::KB, acc, wm, wn, lane);
       }
       if (more) {
         wait_vm<0>();
@@ -1742,7 +1745,7 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
       }
     }
     if constexpr (kCarryStep)
-      if (active && nk > 0) mma_flush<T, C, kRows>(acc, fr);
+      if (active && nk > 0) mma_flush<T, C>(acc, fr);
   }
   next(smem, w, lane);
   char* slab = slab_of<C, kArray>(smem, w);
@@ -1752,6 +1755,14 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
     // stages are free and each wave takes kStageSlabBytes of them.
     __syncthreads();
     slab = smem + w * kStageSlabBytes;
+  } else if constexpr (HasEpiStores<P>::value) {
+    // such an epilogue needs a slab: where the LDS has no room for one beside
+    // the stages, those (the launch is not persistent: no copies in flight)
+    if (slab == nullptr) {
+      static_assert(C::NW * kSlabBytes <= C::kLds, "slabs in the stages");
+      __syncthreads();
+      slab = smem + w * kSlabBytes;
+    }
   }
   p.epilogue(g, t, acc, wm, wn, lane, slab);
 }
@@ -1846,8 +1857,8 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
     GemmArgs g) {
   static_assert(C::kThreads == CQ::kThreads && C::kLds >= CQ::kLds, "quarter tiles must fit");
   static_assert(CQ::BM * 2 == C::BM && CQ::BN * 2 == C::BN, "quarter tiles of the same grid");
-  // One LDS object: the stages, then the epilogue slabs or (dynamic launches,
-  // whose epilogues take no slab) the next tile index.
+  // One LDS object: the stages, then the epilogue slabs, the first of which
+  // (dynamic launches) also holds the next tile index between epilogues.
   // With a second __shared__ variable the compiler scopes every LDS access
   // by variable and then cannot tell a fragment read of one stage from the
   // copies into the other, so each K step's reads would wait for the next
@@ -1870,24 +1881,17 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
       }
     }
   } else if (kDynamic<C, P> && g.tile_ctr != nullptr) {
-    // Three LDS words: slot 2 for grab(), slots 0 and 1 for the tile index
-    // fetched ahead, alternating from one tile to the next.  A wave reads
-    // slot p after the barrier that follows thread 0's write; thread 0 writes
-    // slot p again two tiles later, after it has passed the next tile's
-    // barrier, which every wave reaches only after its read - even when the
-    // tile in between has no K steps (an expert without rows) and so no K-loop
-    // barrier.
+    // One LDS word for the tile index that thread 0 takes: every wave reads it
+    // between the barrier that follows the write and a second one, after which
+    // it may be written again (and wave 0's epilogue slab may overwrite it).
     int32_t* s_next = reinterpret_cast<int32_t*>(smem + C::kLds);
-    // thread 0 takes a tile index; every wave reads it after a barrier (and
-    // again before thread 0 may overwrite it)
     auto grab = [&]() {
-      if (threadIdx.x == 0) s_next[2] = atomicAdd(g.tile_ctr, 1);
+      if (threadIdx.x == 0) *s_next = atomicAdd(g.tile_ctr, 1);
       __syncthreads();
-      const int v = __builtin_amdgcn_readfirstlane(s_next[2]);  // uniform: scalar tile state
+      const int v = __builtin_amdgcn_readfirstlane(*s_next);  // uniform: scalar tile state
       __syncthreads();
       return v;
     };
-    int par = 0;
     P p;
     Tile t;
     int v = grab();
@@ -1916,9 +1920,11 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
       int vn = nmain;
       bool okn = false;
       run_located<T, C, P>(g, smem, p, t, pre, [&](char* sm, int w, int lane) {
-        if (threadIdx.x == 0) s_next[par] = ahead;
+        if (threadIdx.x == 0) *s_next = ahead;
         __syncthreads();  // s_next is visible; every wave is past its last MFMA
-        vn = __builtin_amdgcn_readfirstlane(s_next[par]);
+        vn = __builtin_amdgcn_readfirstlane(*s_next);
+        asm volatile("" : "+s"(vn) : : "memory");  // read before the barrier
+        __builtin_amdgcn_s_barrier();
         okn = vn < nmain && pn.locate(g, tn, vn, nmain);
         if (okn) {
           pn.init(g, tn, w, lane);
@@ -1932,10 +1938,9 @@ __attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_ge
       }
       v = vn;
       pre = okn;
-      par ^= 1;
       // without a prefetched tile, the grab in the locate loop above (or the
       // quarter-tile barrier below) separates this tile's LDS use from the
-      // next one's, and lets every wave read s_next before it changes
+      // next one's
       if (!okn) __syncthreads();
     }
     if (split) {
