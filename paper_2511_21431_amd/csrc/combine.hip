@@ -16,6 +16,13 @@
 
 namespace memfine {
 
+// 16 bytes of a row that nothing reads again: a non-temporal load leaves the
+// caches to what the next kernels read (a step of 3001 tokens, h 1600, k 5,
+// 20 experts: 2.08 -> 2.05 ms).
+template <typename T> __device__ __forceinline__ u32x4_t load_last(const T* p) {
+  return __builtin_nontemporal_load((const u32x4_t*)p);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y,
                                                       const int32_t* __restrict__ row_of_slot,
@@ -44,7 +51,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y,
 #pragma unroll
     for (int j = 0; j < 8; ++j)  // (k is uniform: no load past the token's slots;
       if (j0 + j < k)            // a dropped slot, r < 0, reads row 0 with weight 0)
-        v[j] = *(const u32x4_t*)(y + (int64_t)(r[j] < 0 ? 0 : r[j]) * h + c * V);
+        v[j] = load_last(y + (int64_t)(r[j] < 0 ? 0 : r[j]) * h + c * V);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (r[j] < 0) continue;
@@ -97,7 +104,7 @@ __global__ __launch_bounds__(256) void unpermute_kernel(const T* __restrict__ dx
 #pragma unroll
     for (int j = 0; j < 8; ++j)  // (k is uniform: no load past the token's slots;
       if (j0 + j < k)            // a dropped slot, r < 0, reads row 0 and is skipped)
-        v[j] = *(const u32x4_t*)(dxp + (int64_t)(r[j] < 0 ? 0 : r[j]) * h + c * V);
+        v[j] = load_last(dxp + (int64_t)(r[j] < 0 ? 0 : r[j]) * h + c * V);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (r[j] < 0) continue;
