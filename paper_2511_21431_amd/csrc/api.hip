@@ -268,7 +268,8 @@ ChunkBuffers carve(void* base, const Layout& L) {
   c.ag = b + L.off[Layout::kAg];
   c.dxp = b + L.off[Layout::kDxp];
   c.dgp = (float*)(b + L.off[Layout::kDgp]);
-  c.ctr = (int32_t*)(b + L.off[Layout::kCtr]);
+  c.ctr = L.size[Layout::kCtr] ? (int32_t*)(b + L.off[Layout::kCtr]) : nullptr;
+  c.m.clear = c.ctr;
   c.off_c = (int32_t*)(b + L.off[Layout::kOffC]);
   c.order_c = (int32_t*)(b + L.off[Layout::kOrderC]);
   c.wexp = (int32_t*)(b + L.off[Layout::kWexp]);
@@ -637,12 +638,8 @@ int memfine_count(const memfine_shape* shape, const int32_t* d_idx, int32_t* d_w
   if (!d_work || !h_counts || (shape->T > 0 && !d_idx)) return MEMFINE_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
   const int64_t nslots = shape->T * shape->k;
-  {
-    KernelTimer kt(MEMFINE_K_COUNT, s, 0.0, 4.0 * nslots);
-    if (launch_count(d_idx, nslots, shape->E, d_work, s) != hipSuccess) return MEMFINE_ERR_HIP;
-  }
   // the counts come back through a pinned buffer (a direct copy; a pageable
-  // destination is staged by the runtime)
+  // destination is staged by the runtime), held until they have been read
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MEMFINE_ERR_HIP;
   std::lock_guard<std::mutex> lk(g_pinned_mu);
@@ -652,8 +649,17 @@ int memfine_count(const memfine_shape* shape, const int32_t* d_idx, int32_t* d_w
     host = nullptr;
     return MEMFINE_ERR_HIP;
   }
-  if (hipMemcpyAsync(host, d_work, (shape->E + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s) !=
-      hipSuccess)
+  // few slots: one kernel counts them and writes both results; many need the
+  // whole chip, and a copy of the sums
+  const bool one = nslots <= kCountOneSlots;
+  {
+    KernelTimer kt(MEMFINE_K_COUNT, s, 0.0, 4.0 * nslots);
+    if ((one ? launch_count_one(d_idx, nslots, shape->E, d_work, host, s)
+             : launch_count(d_idx, nslots, shape->E, d_work, s)) != hipSuccess)
+      return MEMFINE_ERR_HIP;
+  }
+  if (!one && hipMemcpyAsync(host, d_work, (shape->E + 1) * sizeof(int32_t), hipMemcpyDeviceToHost,
+                             s) != hipSuccess)
     return MEMFINE_ERR_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return MEMFINE_ERR_HIP;
   for (int e = 0; e < shape->E; ++e) h_counts[e] = host[e];
@@ -687,6 +693,7 @@ int memfine_dispatch(const memfine_shape* shape, const int32_t* d_idx, int64_t t
   m.offsets = d_offsets;
   m.sorted_slot = d_sorted_slot;
   m.row_of_slot = d_row_of_slot;
+  m.clear = nullptr;
   hipError_t err;
   {
     KernelTimer kt(MEMFINE_K_DISPATCH, s, 0.0, dispatch_work(n).bytes);
@@ -806,7 +813,7 @@ int moe_fwd_experts(const memfine_shape& S, int32_t chunks, const void* d_X, con
     }
     const ChunkBuffers cb = carve(ws, L);
     err = launch_chunk_view(mb.m.offsets, S.E, (int)p0, (int)p1, c == 0, 0, mb.off_c, mb.order_c,
-                            mb.wexp, mb.wmode, s);
+                            mb.wexp, mb.wmode, nullptr, s);
     GemmArgs g = gemm_args(S, n, cb, opt);
     g.offsets = mb.off_c;
     g.order = mb.order_c;
@@ -907,8 +914,8 @@ struct BwdWork {
 };
 // A chunk's backward GEMMs, after its dispatch: FC2 dgrad, the FC1
 // recomputation with the SwiGLU backward, the two weight gradients and the
-// FC1 dgrad (the last three on side streams, or in one launch, as the
-// launch options say).
+// FC1 dgrad (the last three on side streams, two in one launch, as the launch
+// options say, or, for small problems, all three in one launch).
 hipError_t bwd_gemms(const GemmArgs& g, const ChunkBuffers& cb, const memfine_launch_options& opt,
                      const BwdWork& w, hipStream_t s) {
   hipError_t err;
@@ -962,6 +969,14 @@ hipError_t bwd_gemms(const GemmArgs& g, const ChunkBuffers& cb, const memfine_la
           if (err == hipSuccess) err = e2;
         }
       }
+    }
+    return err;
+  }
+  if (!opt.pair && bwd_merges(g)) {
+    if (err == hipSuccess) {
+      KernelTimer kt(MEMFINE_K_FC1_BWD, s, w.fc1d.flops + w.fc1w.flops + w.fc2w.flops,
+                     w.fc1d.bytes + w.fc1w.bytes + w.fc2w.bytes);
+      err = launch_bwd_merged(g, s);
     }
     return err;
   }
@@ -1036,7 +1051,7 @@ int moe_bwd_experts(const memfine_shape& S, int32_t chunks, const void* d_X, con
     }
     const ChunkBuffers cb = carve(ws, L);
     err = launch_chunk_view(mb.m.offsets, S.E, (int)p0, (int)p1, c == 0, accumulate_dW, mb.off_c,
-                            mb.order_c, mb.wexp, mb.wmode, s);
+                            mb.order_c, mb.wexp, mb.wmode, cb.ctr, s);
     GemmArgs g = gemm_args(S, n, cb, opt);
     g.offsets = mb.off_c;
     g.order = mb.order_c;

@@ -2069,15 +2069,36 @@ template <typename T, class C> using FC2WAdd = ProbWgrad<T, C, false, 1>;
 template <typename T, class C> using FC1WNew = ProbWgrad<T, C, true, 0>;
 template <typename T, class C> using FC1WAdd = ProbWgrad<T, C, true, 1>;
 
+// FC1 dgrad and both weight gradients of a small problem, one tile per
+// workgroup: nd, n1 and n2 of them.
+template <typename T, class C, class PD, class PW1, class PW2>
+__global__ __launch_bounds__(C::kThreads, C::kMinWaves)
+__attribute__((amdgpu_waves_per_eu(C::kMinWaves, C::kMinWaves))) void grouped_gemm_bwd_kernel(
+    GemmArgs g, int nd, int n1) {
+  __shared__ __attribute__((aligned(1024))) char smem[C::kLds + kSlabArea<C>];
+  const int i = blockIdx.x;
+  if (i < nd) {
+    const int n = min(nd, PD::total_tiles(g));
+    if (i < n) run_tile<T, C, PD>(g, smem, i, n);
+  } else if (i < nd + n1) {
+    run_tile<T, C, PW1>(g, smem, i - nd, n1);
+  } else {
+    run_tile<T, C, PW2>(g, smem, i - nd - n1, gridDim.x - nd - n1);
+  }
+}
+template <typename T, class C> hipError_t launch_bwd_cfg(const GemmArgs& g, hipStream_t s) {
+  const int nd = ProbFC1Dgrad<T, C>::grid(g), n1 = FC1W<T, C>::grid(g), n2 = FC2W<T, C>::grid(g);
+  if (nd + n1 + n2 <= 0) return hipSuccess;
+  grouped_gemm_bwd_kernel<T, C, ProbFC1Dgrad<T, C>, FC1W<T, C>, FC2W<T, C>>
+      <<<nd + n1 + n2, C::kThreads, 0, s>>>(g, nd, n1);
+  return hipGetLastError();
+}
+
 template <template <typename, class> class PT, class C, class CQ>
 hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
   const int bound = PT<bf16_t, C>::grid(g);
   if (bound <= 0) return hipSuccess;
   const bool dynamic = kDynamic<C, PT<bf16_t, C>> && g.tile_ctr != nullptr;
-  if (dynamic) {  // the tile counter starts at 0 for this launch
-    const hipError_t err = launch_fill_i32(g.tile_ctr, 1, 0, s);
-    if (err != hipSuccess) return err;
-  }
   // (a grid of at most cus / 2 tiles runs as 4 bound quarter tiles: with one
   // workgroup per tile half of the CUs or more had none - 128 tiles of the
   // router's logits at 32768 tokens, h 7168: 409 us, one round of 256: 255 us)
@@ -2167,6 +2188,23 @@ hipError_t launch_pair(const GemmArgs& g_in, hipStream_t s) {
 
 
 }  // namespace
+
+// The three products that read what the recomputation wrote, as one launch
+// where each alone takes the small tiles because it would leave CUs idle: one
+// launch's last round and latency instead of three.
+bool bwd_merges(const GemmArgs& g) {
+  if (g.tile_override != MEMFINE_TILE_AUTO) return false;
+  if (g.dtype != 0)
+    return ProbFC1Dgrad<float, Small>::grid(g) < kF32SmallGrid &&
+           FC1W<float, Small>::grid(g) < kF32SmallGrid && FC2W<float, Small>::grid(g) < kF32SmallGrid;
+  return g.n < (int64_t)kMidRows * g.E && FC1W<float, Big8>::grid(g) < kWgradGrid &&
+         FC2W<float, Big8>::grid(g) < kWgradGrid;
+}
+hipError_t launch_bwd_merged(const GemmArgs& g_in, hipStream_t s) {
+  GemmArgs g = g_in;
+  if (g.raster < 0) g.raster = 0;
+  return g.dtype != 0 ? launch_bwd_cfg<float, F32N>(g, s) : launch_bwd_cfg<bf16_t, Small>(g, s);
+}
 
 int dgate_partials(int F) { return (F + 31) / 32; }
 

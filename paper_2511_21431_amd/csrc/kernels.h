@@ -23,6 +23,13 @@ inline int dispatch_blocks(int64_t n) {
   return (int)((n + spb - 1) / spb);
 }
 
+// Up to this many slots (and kOneLaunchExperts experts, whose order one
+// workgroup finds) the dispatch is one launch: every workgroup reads all the
+// slots' ids, 8 dependent rounds at most.  512 slots: 4.1 us against 3.1 + 3.7
+// for histogram and scatter; 7500 slots in a step (ids from memory): 14 us
+// against 4.1 + 6.1.
+constexpr int kOneLaunchSlots = 2048, kOneLaunchExperts = 256;
+
 // Per-chunk routing metadata produced by the dispatch kernels; all device.
 struct ChunkMeta {
   int32_t* bcount;       // [E * nb]  per-workgroup expert histograms (expert-major)
@@ -34,9 +41,17 @@ struct ChunkMeta {
   int32_t* row_of_slot;  // [n]       grouped row of the chunk's i-th slot
   int32_t* tok_of_row;   // [n]       token of each grouped row
   float* gate_of_row;    // [n]       gate of each grouped row
+  int32_t* clear;        // [2]       set to 0 beside the dispatch, or null
 };
 
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
+// Up to kCountOneSlots slots one workgroup counts, and writes the E + 1 counts
+// to `work` and to the pinned `host`: 2.0 us at 2048 slots against 2.6 + 4.2 for
+// clearing and counting, and no copy (the whole call 26 -> 20 us); at 16000
+// slots 7.2 us, where the call gains nothing.
+constexpr int64_t kCountOneSlots = 8192;
+hipError_t launch_count_one(const int32_t* idx, int64_t nslots, int E, int32_t* work, int32_t* host,
+                            hipStream_t s);
 hipError_t launch_count(const int32_t* idx, int64_t nslots, int E, int32_t* work, hipStream_t s);
 // Dispatch of slots [slot0, slot0 + n) of the flat idx array (one chunk).
 hipError_t launch_dispatch(const int32_t* idx, const float* gates, int64_t slot0, int n, int E,
@@ -48,10 +63,11 @@ hipError_t launch_dispatch(const int32_t* idx, const float* gates, int64_t slot0
 // p0), its experts with a weight-gradient tile first, by descending row
 // count [E], their number [1], and each expert's weight-gradient mode [E]
 // (0: no tile, 1: overwrite dW, 2: add to dW).  `first`: the first chunk
-// (overwrites the dW of experts without rows unless `accumulate`).
+// (overwrites the dW of experts without rows unless `accumulate`).  `clear`:
+// two ints set to 0, or null.
 hipError_t launch_chunk_view(const int32_t* offsets, int E, int p0, int p1, int first,
                              int accumulate, int32_t* offsets_c, int32_t* order_c,
-                             int32_t* wexperts, int32_t* wmode, hipStream_t s);
+                             int32_t* wexperts, int32_t* wmode, int32_t* clear, hipStream_t s);
 
 // Gate-weighted combine, Y[t0 + i] = sum_j g[t, j] * y[row_of_slot[i*k + j]].
 hipError_t launch_combine(int dtype, const void* y, const int32_t* row_of_slot, const float* gates,
@@ -103,8 +119,9 @@ struct GemmArgs {
   int raster;        // tile order: -1 per problem; 0 row-major; 1..3 XCD blocks, groups of 4/8/16 m-tiles; 4 XCD blocks, row-major
   int cus;           // compute units of the device
   int split_tail;    // 1: row-grouped GEMMs run a short last round as quarter tiles
-  int32_t* tile_ctr; // weight gradients: device tile counter (one int) for a dynamic
-                     // persistent launch, or null for one tile per workgroup
+  int32_t* tile_ctr; // weight gradients: device tile counter (one int, 0 when the launch
+                     // starts) for a dynamic persistent launch, or null for one tile per
+                     // workgroup
 };
 
 int dgate_partials(int F);
@@ -151,6 +168,10 @@ hipError_t launch_fc2_dgrad(const GemmArgs& g, hipStream_t s);
 hipError_t launch_fc2_wgrad(const GemmArgs& g, hipStream_t s);
 hipError_t launch_fc1_wgrad(const GemmArgs& g, hipStream_t s);
 hipError_t launch_fc1_dgrad(const GemmArgs& g, hipStream_t s);
+// FC1 dgrad and both weight gradients in one launch: true for problems so small
+// that each would leave CUs idle.
+bool bwd_merges(const GemmArgs& g);
+hipError_t launch_bwd_merged(const GemmArgs& g, hipStream_t s);
 // FC1 dgrad and FC1 wgrad in one launch (independent problems).
 hipError_t launch_fc1_dgrad_wgrad(const GemmArgs& g, hipStream_t s);
 

@@ -7,7 +7,8 @@
 // cursors: each workgroup owns a fixed, ordered range of slots; a first pass
 // counts experts per workgroup, a scan turns the (expert, workgroup) counts
 // into first output rows (a single-workgroup kernel, or, while there are few
-// counts, each workgroup of the second pass for itself), and a second pass ranks
+// counts, each workgroup of the second pass for itself; with few slots the
+// second pass also counts them and is the only one), and a second pass ranks
 // the slots of each workgroup in order with wavefront ballots (the set of
 // lanes holding the same expert id is found bit by bit) and per-wave counts
 // in LDS.
@@ -36,6 +37,23 @@ __global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ 
   __syncthreads();
   for (int i = threadIdx.x; i <= E; i += blockDim.x)
     if (hist[i]) atomicAdd(&work[i], hist[i]);
+}
+
+// The same in one workgroup, which writes the E + 1 counts itself, also into
+// the host's pinned buffer: no clearing launch and no copy.
+__global__ __launch_bounds__(1024) void count_one_kernel(const int32_t* __restrict__ idx, int nslots,
+                                                         int E, int32_t* __restrict__ work,
+                                                         int32_t* __restrict__ host) {
+  __shared__ int32_t hist[1025];  // E <= 1024
+  for (int i = threadIdx.x; i <= E; i += 1024) hist[i] = 0;
+  __syncthreads();
+#pragma unroll 4
+  for (int s = threadIdx.x; s < nslots; s += 1024) {
+    const int e = idx[s];
+    atomicAdd(&hist[((unsigned)e < (unsigned)E) ? e : E], 1);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i <= E; i += 1024) work[i] = host[i] = hist[i];
 }
 
 // bcount[e * nb + b] = #slots of expert e in workgroup b's slot range.
@@ -143,37 +161,55 @@ __device__ int32_t block_exclusive_scan(int32_t* v, int m, int32_t* part) {
 //   + slots of that expert in earlier waves of this round + its rank among
 //   the lanes of its own wave holding the same expert.
 //
-// kFused: the workgroup derives its first rows from the per-block counts
-// itself (the total of every expert over all blocks, scanned over experts,
-// plus the expert's slots in earlier blocks), and workgroup 0 writes counts,
-// offsets and order, which saves the single-workgroup scan launch; used
-// while E * nb is small enough that every workgroup reading all counts is
-// cheap.
-template <bool kFused>
+// kFrom says where a workgroup's first rows come from:
+//   kScanned  the scan kernel's bstart;
+//   kCounts   the workgroup derives them from the per-block counts itself (the
+//             total of every expert over all blocks, scanned over experts,
+//             plus the expert's slots in earlier blocks), and workgroup 0
+//             writes counts, offsets and order: no scan launch;
+//   kSlots    the same from the slots themselves, which every workgroup
+//             reads: one launch in all.
+// `clear`: two ints that workgroup 0 sets to 0, or null.
+enum RowsFrom { kScanned, kCounts, kSlots };
+template <int kFrom>
 __global__ __launch_bounds__(256) void scatter_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ gates, int n, int E, int k,
     int slot0, int nb, int spb, const int32_t* __restrict__ bstart, int32_t* __restrict__ sorted_slot,
     int32_t* __restrict__ row_of_slot, int32_t* __restrict__ tok_of_row,
     float* __restrict__ gate_of_row, const int32_t* __restrict__ bcount,
-    int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ order) {
+    int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ order,
+    int32_t* __restrict__ clear) {
   extern __shared__ int32_t sh[];
   int32_t* run = sh;      // [E]     next row per expert for this workgroup
   int32_t* wc = sh + E;   // [4][E]  per-wave counts of the current round
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if constexpr (kFused) {
+  if (clear != nullptr && blockIdx.x == 0 && tid < 2) clear[tid] = 0;
+  if constexpr (kFrom != kScanned) {
     int32_t* tot = wc;           // [E] slots of each expert in the chunk, then its first row
     int32_t* pre = wc + E;       // [E] the expert's slots in the workgroups before this one
     int32_t* cnt = wc + 2 * E;   // [E] the counts, kept for the order
     __shared__ int32_t spart[256];
     for (int e = tid; e < E; e += 256) tot[e] = pre[e] = 0;
     __syncthreads();
-    const int64_t m = (int64_t)E * nb;
-    for (int64_t i = tid; i < m; i += 256) {
-      const int32_t v = bcount[i];
-      if (v) {
-        const int e = (int)(i / nb), b = (int)(i % nb);
-        atomicAdd(&tot[e], v);
-        if (b < (int)blockIdx.x) atomicAdd(&pre[e], v);
+    if constexpr (kFrom == kSlots) {
+      const int first = blockIdx.x * spb;
+#pragma unroll 4
+      for (int i = tid; i < n; i += 256) {
+        const int e = idx[i];
+        if ((unsigned)e < (unsigned)E) {
+          atomicAdd(&tot[e], 1);
+          if (i < first) atomicAdd(&pre[e], 1);
+        }
+      }
+    } else {
+      const int64_t m = (int64_t)E * nb;
+      for (int64_t i = tid; i < m; i += 256) {
+        const int32_t v = bcount[i];
+        if (v) {
+          const int e = (int)(i / nb), b = (int)(i % nb);
+          atomicAdd(&tot[e], v);
+          if (b < (int)blockIdx.x) atomicAdd(&pre[e], v);
+        }
       }
     }
     __syncthreads();
@@ -251,32 +287,38 @@ hipError_t launch_count(const int32_t* idx, int64_t nslots, int E, int32_t* work
   return hipGetLastError();
 }
 
+hipError_t launch_count_one(const int32_t* idx, int64_t nslots, int E, int32_t* work, int32_t* host,
+                            hipStream_t s) {
+  if (E > 1024 || nslots > kCountOneSlots) return hipErrorInvalidValue;
+  count_one_kernel<<<1, 1024, 0, s>>>(idx, (int)nslots, E, work, host);
+  return hipGetLastError();
+}
+
 hipError_t launch_dispatch(const int32_t* idx, const float* gates, int64_t slot0, int n, int E,
                            int k, const ChunkMeta& m, hipStream_t s) {
   const int nb = dispatch_blocks(n), spb = dispatch_slots_per_block(n);
   const int32_t* cidx = idx + slot0;
+  auto scatter = [&](auto kernel) {
+    kernel<<<nb, 256, 5 * E * sizeof(int32_t), s>>>(
+        cidx, gates ? gates + slot0 : nullptr, n, E, k, (int)slot0, nb, spb, m.bstart,
+        m.sorted_slot, m.row_of_slot, m.tok_of_row, m.gate_of_row, m.bcount, m.counts, m.offsets,
+        m.order, m.clear);
+    return hipGetLastError();
+  };
+  // few slots: every workgroup counts them all
+  if (nb > 0 && n <= kOneLaunchSlots && E <= kOneLaunchExperts)
+    return scatter(scatter_kernel<kSlots>);
   if (nb > 0) {
     block_hist_kernel<<<nb, 256, E * sizeof(int32_t), s>>>(cidx, n, E, nb, spb, m.bcount);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
   // small E x nb: the scatter workgroups scan the counts themselves
-  const bool fused = nb > 0 && (int64_t)E * nb <= 16384;
-  if (!fused) {
-    scan_kernel<<<1, 1024, 0, s>>>(m.bcount, E, nb, n, m.bstart, m.counts, m.offsets, m.order);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess || nb == 0) return err;
-    scatter_kernel<false><<<nb, 256, 5 * E * sizeof(int32_t), s>>>(
-        cidx, gates ? gates + slot0 : nullptr, n, E, k, (int)slot0, nb, spb, m.bstart,
-        m.sorted_slot, m.row_of_slot, m.tok_of_row, m.gate_of_row, nullptr, nullptr, nullptr,
-        nullptr);
-  } else {
-    scatter_kernel<true><<<nb, 256, 5 * E * sizeof(int32_t), s>>>(
-        cidx, gates ? gates + slot0 : nullptr, n, E, k, (int)slot0, nb, spb, m.bstart,
-        m.sorted_slot, m.row_of_slot, m.tok_of_row, m.gate_of_row, m.bcount, m.counts, m.offsets,
-        m.order);
-  }
-  return hipGetLastError();
+  if (nb > 0 && (int64_t)E * nb <= 16384) return scatter(scatter_kernel<kCounts>);
+  scan_kernel<<<1, 1024, 0, s>>>(m.bcount, E, nb, n, m.bstart, m.counts, m.offsets, m.order);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess || nb == 0) return err;
+  return scatter(scatter_kernel<kScanned>);
 }
 
 // The view of an expert-ordered chunk, rows [p0, p1) of the layer's grouped
@@ -286,7 +328,7 @@ hipError_t launch_dispatch(const int32_t* idx, const float* gates, int64_t slot0
 __global__ __launch_bounds__(1024) void chunk_view_kernel(
     const int32_t* __restrict__ offsets, int E, int p0, int p1, int first, int accumulate,
     int32_t* __restrict__ offsets_c, int32_t* __restrict__ order_c,
-    int32_t* __restrict__ wexperts, int32_t* __restrict__ wmode) {
+    int32_t* __restrict__ wexperts, int32_t* __restrict__ wmode, int32_t* __restrict__ clear) {
   __shared__ int32_t key[1024];
   __shared__ int32_t n_tiles;
   const int e = threadIdx.x;
@@ -317,14 +359,15 @@ __global__ __launch_bounds__(1024) void chunk_view_kernel(
     order_c[rank] = e;
   }
   if (e == 0) *wexperts = n_tiles;
+  if (e < 2 && clear != nullptr) clear[e] = 0;
 }
 
 hipError_t launch_chunk_view(const int32_t* offsets, int E, int p0, int p1, int first,
                              int accumulate, int32_t* offsets_c, int32_t* order_c,
-                             int32_t* wexperts, int32_t* wmode, hipStream_t s) {
+                             int32_t* wexperts, int32_t* wmode, int32_t* clear, hipStream_t s) {
   if (E < 1 || E > 1024) return hipErrorInvalidValue;
   chunk_view_kernel<<<1, 1024, 0, s>>>(offsets, E, p0, p1, first, accumulate, offsets_c, order_c,
-                                       wexperts, wmode);
+                                       wexperts, wmode, clear);
   return hipGetLastError();
 }
 

@@ -115,6 +115,68 @@ def test_f32_tile_shape_by_grid(mf, T):
     _check_bwd(mf, w, 40 + T, 1, False)
 
 
+# Dispatch in one launch up to 2048 slots and 256 experts, and the count in one
+# workgroup up to 8192 slots: both sides of each line, dropped ids among them,
+# a chunk that starts inside the ids, and one expert taking every slot.
+@pytest.mark.parametrize("T,k,E", [(1, 1, 1), (512, 4, 256), (512, 4, 257), (683, 3, 9),
+                                   (1024, 8, 300), (2731, 3, 64), (4, 1, 1024)])
+@pytest.mark.parametrize("hot", [False, True])
+def test_dispatch_and_count_lines(mf, T, k, E, hot):
+    t = torch()
+    log(f"dispatch lines T={T} k={k} E={E} hot={hot}")
+    rng = np.random.default_rng(T * k + E)
+    idx = np.full((T, k), E - 1) if hot else rng.integers(0, E, size=(T, k))
+    idx = idx.astype(np.int32)
+    s = mf.make_shape(T, 64, 64, E, k, mf.BF16)
+    work = t.full((E + 1,), -7, dtype=t.int32, device="cuda")
+    assert mf.memfine_count(s, t.from_numpy(idx).cuda(), work).tolist() == \
+        om.expert_counts(idx, E).tolist()
+    assert work.cpu().numpy().tolist() == om.expert_counts(idx, E).tolist() + [0]
+    if T * k > 2 and not hot:
+        idx[0, 0], idx[-1, -1] = E, -1
+        with pytest.raises(mf.MemfineError):
+            mf.memfine_count(s, t.from_numpy(idx).cuda(), work)
+        assert int(work[E]) == 2
+    for t0, t1 in ((0, T), (T // 3, T)):
+        n = (t1 - t0) * k
+        out = [t.full((m,), -7, dtype=t.int32, device="cuda") for m in (E, E + 1, n, n)]
+        mf.memfine_dispatch(s, t.from_numpy(idx).cuda(), t0, t1, *out)
+        c, o, ss, rs = (x.cpu().numpy() for x in out)
+        flat = idx.reshape(-1)[t0 * k:t1 * k]
+        ok = (flat >= 0) & (flat < E)
+        order = np.argsort(np.where(ok, flat, E), kind="stable")[:int(ok.sum())]
+        assert c.tolist() == np.bincount(flat[ok], minlength=E).tolist()
+        assert o.tolist() == np.concatenate(([0], np.cumsum(c))).tolist()
+        assert ss[:order.size].tolist() == (order + t0 * k).tolist()
+        want = np.full(n, -1)
+        want[order] = np.arange(order.size)
+        assert rs.tolist() == want.tolist()
+
+
+# FC1 dgrad and both weight gradients in one launch for small problems: the
+# line of each of its conditions (rows per expert 320, fp32 grids), the bits
+# of the separate launches (forced by a tile option in bf16), both chunk orders.
+@pytest.mark.parametrize("T,E,h,F,dtype", [(639, 4, 192, 320, "bf16"), (640, 4, 192, 320, "bf16"),
+                                           (50, 5, 64, 64, "bf16"), (300, 3, 192, 128, "f32"),
+                                           (200, 70, 64, 64, "f32")])
+def test_bwd_in_one_launch(mf, T, E, h, F, dtype):
+    w = mw.Workload("merge", T=T, h=h, F=F, E=E, k=2, dtype=dtype, routing="dirichlet")
+    log(f"one launch T={T} E={E} {dtype}")
+    for C, order in ((1, mf.CHUNK_TOKENS), (3, mf.CHUNK_TOKENS), (2, mf.CHUNK_EXPERTS)):
+        for accumulate in (False, True):
+            _check_bwd(mf, w, 50 + T + E, C, accumulate, chunk_order=order)
+    if dtype == "bf16":
+        dev = device_case(w, mw.make_case(w, 50 + T + E))
+        one = {k: host(v) for k, v in run_bwd(w, dev, 1).items()}
+        try:
+            mf.memfine_set_launch_options(tile=mf.TILE_128)
+            three = {k: host(v) for k, v in run_bwd(w, dev, 1).items()}
+        finally:
+            mf.memfine_set_launch_options()
+        for key in one:
+            assert np.array_equal(one[key], three[key]), key
+
+
 # Router: both sides of the logits GEMM's tile rules (one round of 64-row, then
 # of 128-row tiles), the dz rows' 64-token workgroups, and routers too small
 # for a whole tile.  T = 1 and 65 also at 96 logits (dX from the dz kernel's
