@@ -2094,6 +2094,201 @@ template <typename T, class C> hipError_t launch_bwd_cfg(const GemmArgs& g, hipS
   return hipGetLastError();
 }
 
+// Router dX (+)= D Wr for many tokens (bf16, E = 16 KS).  A wave keeps 64 rows of
+// D, all of K, in registers and the workgroup's 4 waves walk the columns in
+// blocks of 128, whose E rows of Wr go through LDS (direct copies, the next
+// block's in flight): the short reduction (E <= 256) needs no K loop, and what
+// a block waits for is its dX rows' way to memory.  As a grouped GEMM of 256 x
+// 256 tiles each tile's 4 K steps and epilogue followed one another and D and
+// Wr passed the L2 for every tile: 32768 tokens, h 7168, 256 logits 183 us
+// (adding: 314), now 162 (255); dX is 470 MB.  kStream: non-temporal stores of
+// dX, for results larger than the Infinity Cache (kStreamBytes), which would
+// displace the X that the weight gradient reads next: this kernel 173 us then,
+// the forward and backward at that size 482 -> 458 us.
+template <int KS, bool kStream>
+__global__ __launch_bounds__(256, 1) void router_dx_kernel(const bf16_t* D, const bf16_t* Wr,
+                                                           int64_t T, int h, int accumulate,
+                                                           bf16_t* dX) {
+  constexpr int E = 16 * KS, kStage = E * 256;  // LDS: E rows of 128 columns
+  __shared__ __attribute__((aligned(1024))) char smem[2 * kStage + 4 * kSlabBytes];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row0 = (int64_t)blockIdx.x * 256 + w * 64;
+  const int nblocks = (h + 127) / 128;
+  const int b0 = (int)((int64_t)blockIdx.y * nblocks / gridDim.y);
+  const int b1 = (int)((int64_t)(blockIdx.y + 1) * nblocks / gridDim.y);
+  // Wr block: copy instruction i of wave w brings k-rows 16 i + 4 w .. + 3
+  const uint32_t ld = (uint32_t)h * 2;
+  const __amdgpu_buffer_rsrc_t wrs = make_rsrc(Wr, (int64_t)E * ld);
+  const int kr = 4 * w + (lane >> 4);
+  const int col = ((lane & 15) ^ ks_sw<2>(kr)) * 8;
+  const uint32_t voff = (uint32_t)kr * ld + (uint32_t)col * 2;
+  auto issue = [&](int b) {
+    const uint32_t vo = b * 128 + col < h ? voff : kOOB;
+    char* st = smem + (b & 1) * kStage;
+#pragma clang loop unroll(full)
+    for (int i = 0; i < KS; ++i)
+      load_lds16(wrs, st + (i * 4 + w) * 1024, vo, (uint32_t)b * 256 + (uint32_t)i * 16 * ld);
+  };
+  issue(b0);
+  // D rows (rows past T read the last one; their results are not stored)
+  bf16x8_t a[KS][2];
+#pragma clang loop unroll(full)
+  for (int i = 0; i < 2; ++i) {
+    int64_t r = row0 + i * 32 + (lane & 31);
+    r = r < T ? r : T - 1;
+    const bf16_t* d = D + r * E + (lane >> 5) * 8;
+#pragma clang loop unroll(full)
+    for (int k = 0; k < KS; ++k) a[k][i] = *(const bf16x8_t*)(d + k * 16);
+  }
+  const int rows = (int)(row0 < T ? (T - row0 < 64 ? T - row0 : 64) : 0);
+  const __amdgpu_buffer_rsrc_t xrs = make_rsrc(dX + (rows > 0 ? row0 : 0) * h, (int64_t)rows * ld);
+  char* slab = smem + 2 * kStage + w * kSlabBytes;
+  const int rr = lane & 31, half = lane >> 5, unit = lane & 7;
+  constexpr int kStores = 16;  // per block
+  // D and the first block have landed.  (Waited for here: left to the compiler, the
+  // waits for D's registers land inside the loop, where they also wait for the
+  // copies that each block has just issued.)
+  wait_vm<0>();
+  for (int b = b0; b < b1; ++b) {
+    // this block's copies have landed; the previous block's stores may be in flight
+    wait_vm<kStores>();
+    wait_lgkm0();
+    __builtin_amdgcn_s_barrier();
+    // old dX values: 64 rows x 64 columns per half block, 16 bytes a lane
+    u32x4_t old[2][8];
+    auto xoff = [&](int hb, int q) {  // access q: rows 8 q .. + 7, 8 lanes a row
+      const int c = b * 128 + hb * 64 + unit * 8;
+      return c < h ? (uint32_t)(8 * q + (lane >> 3)) * ld + (uint32_t)c * 2 : kOOB;
+    };
+    if (accumulate) {
+#pragma clang loop unroll(full)
+      for (int hb = 0; hb < 2; ++hb)
+#pragma clang loop unroll(full)
+        for (int q = 0; q < 8; ++q) old[hb][q] = load_reg16(xrs, xoff(hb, q), 0);
+    }
+    if (b + 1 < b1) issue(b + 1);
+    const char* st = smem + (b & 1) * kStage;
+#pragma clang loop unroll(full)
+    for (int hb = 0; hb < 2; ++hb) {
+      f32x16_t acc[2][2];
+#pragma clang loop unroll(full)
+      for (int i = 0; i < 2; ++i)
+#pragma clang loop unroll(full)
+        for (int j = 0; j < 2; ++j)
+#pragma clang loop unroll(full)
+          for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+      // the next step's fragments are read under this step's MFMAs
+      bf16x8_t bf[2][2];
+#pragma clang loop unroll(full)
+      for (int j = 0; j < 2; ++j) bf[0][j] = ks_read_bf16<128>(st, hb * 64 + j * 32, 0, lane);
+#pragma clang loop unroll(full)
+      for (int k = 0; k < KS; ++k) {
+        if (k + 1 < KS) {
+#pragma clang loop unroll(full)
+          for (int j = 0; j < 2; ++j)
+            bf[(k + 1) & 1][j] = ks_read_bf16<128>(st, hb * 64 + j * 32, k + 1, lane);
+        }
+#pragma clang loop unroll(full)
+        for (int i = 0; i < 2; ++i)
+#pragma clang loop unroll(full)
+          for (int j = 0; j < 2; ++j) Mma<bf16_t>::mma(bf[k & 1][j], a[k][i], acc[i][j], 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma clang loop unroll(full)
+      for (int k = 0; k + 1 < KS; ++k)
+#pragma clang loop unroll(full)
+        for (int x = 0; x < 4; ++x) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      // out through the slab: 32 rows of 128 bytes (64 columns), as store_rows;
+      // adding, the fp32 sums of 32 columns at a time meet the old values first
+#pragma clang loop unroll(full)
+      for (int i = 0; i < 2; ++i) {
+        if (!accumulate) {
+#pragma clang loop unroll(full)
+          for (int j = 0; j < 2; ++j)
+#pragma clang loop unroll(full)
+            for (int gq = 0; gq < 4; ++gq) {
+              const int byte = j * 64 + gq * 16 + half * 8;
+              float v[4];
+              acc_run(acc[i][j], gq, v);
+              *(u32x2_t*)(slab + rr * 128 + ((((byte >> 4) ^ (rr & 7))) << 4) + (byte & 15)) = pack4(v);
+            }
+          asm volatile("" ::: "memory");  // the writes above before the reads below
+#pragma clang loop unroll(full)
+          for (int q = 0; q < 4; ++q) {
+            const int r = (lane >> 3) + 8 * q;
+            const u32x4_t x = *(const u32x4_t*)(slab + r * 128 + ((unit ^ (r & 7)) << 4));
+            __builtin_amdgcn_raw_buffer_store_b128(x, xrs, xoff(hb, i * 4 + q), 0,
+                                                   kStream ? kNonTemporal : 0);
+          }
+          asm volatile("" ::: "memory");  // the reads above before the next writes
+        } else {
+          // 16 rows x 64 fp32 columns (256-byte rows, 16-byte units XOR-swizzled
+          // by row) at a time
+#pragma clang loop unroll(full)
+          for (int rh = 0; rh < 2; ++rh) {
+            if ((rr >> 4) == rh) {
+#pragma clang loop unroll(full)
+              for (int j = 0; j < 2; ++j)
+#pragma clang loop unroll(full)
+                for (int gq = 0; gq < 4; ++gq) {
+                  float v[4];
+                  acc_run(acc[i][j], gq, v);
+                  const int un = j * 8 + gq * 2 + half, r = rr & 15;
+                  *(f32x4_t*)(slab + r * 256 + ((un ^ r) << 4)) = (f32x4_t){v[0], v[1], v[2], v[3]};
+                }
+            }
+            asm volatile("" ::: "memory");  // the writes above before the reads below
+#pragma clang loop unroll(full)
+            for (int q = 0; q < 2; ++q) {
+              const int r = (lane >> 3) + 8 * q;
+              const f32x4_t lo = *(const f32x4_t*)(slab + r * 256 + (((2 * unit) ^ r) << 4));
+              const f32x4_t hi = *(const f32x4_t*)(slab + r * 256 + (((2 * unit + 1) ^ r) << 4));
+              const int qq = i * 4 + rh * 2 + q;
+              float f[8];
+              unpack16(old[hb][qq], f, (bf16_t*)nullptr);
+#pragma clang loop unroll(full)
+              for (int c = 0; c < 4; ++c) {
+                f[c] += lo[c];
+                f[4 + c] += hi[c];
+              }
+              __builtin_amdgcn_raw_buffer_store_b128(pack16(f, (bf16_t*)nullptr), xrs, xoff(hb, qq), 0, 0);
+            }
+            asm volatile("" ::: "memory");  // the reads above before the next writes
+          }
+        }
+      }
+    }
+  }
+}
+constexpr int64_t kStreamBytes = 256ll << 20;
+// From 8192 tokens; below, 256-row blocks leave CUs idle (4096 tokens, h 2048, 64
+// logits: 18 us against 13 for the grouped GEMM; 8192, h 7168, 256: 42 against 48).
+constexpr int kRouterDxRows = 8192;
+template <int KS> hipError_t launch_router_dx_rows(const GemmArgs& g, hipStream_t s) {
+  const int64_t T = g.n;
+  const int gx = (int)((T + 255) / 256), blocks = (g.F + 127) / 128;
+  // column ranges: the fewest rounds of the CUs per range's work (each range
+  // reads D again)
+  int ny = 1;
+  double best = 1e30;
+  for (int y = 1; y <= 8 && y <= blocks; ++y) {
+    const double cost = (double)((gx * y + g.cus - 1) / g.cus) / y + 0.02 * y;
+    if (cost < best) {
+      best = cost;
+      ny = y;
+    }
+  }
+  const bool stream = !g.accumulate && T * g.F * 2 > kStreamBytes;
+  (stream ? router_dx_kernel<KS, true> : router_dx_kernel<KS, false>)<<<dim3(gx, ny), 256, 0, s>>>(
+      (const bf16_t*)g.dY, (const bf16_t*)g.W2, T, g.F, g.accumulate, (bf16_t*)g.ag);
+  return hipGetLastError();
+}
+
 template <template <typename, class> class PT, class C, class CQ>
 hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
   const int bound = PT<bf16_t, C>::grid(g);
@@ -2222,6 +2417,15 @@ hipError_t launch_fc1_wgrad(const GemmArgs& g, hipStream_t s) {
   return g.accumulate ? launch_auto<FC1WAdd>(g, s) : launch_auto<FC1WNew>(g, s);
 }
 hipError_t launch_router_dx(const GemmArgs& g, hipStream_t s) {
+  if (g.dtype == 0 && g.tile_override == MEMFINE_TILE_AUTO && g.n >= kRouterDxRows) {
+    switch (g.h) {
+      case 64: return launch_router_dx_rows<4>(g, s);
+      case 128: return launch_router_dx_rows<8>(g, s);
+      case 192: return launch_router_dx_rows<12>(g, s);
+      case 256: return launch_router_dx_rows<16>(g, s);
+      default: break;
+    }
+  }
   return launch_auto<ProbRouterDx>(g, s);
 }
 hipError_t launch_router_logits(const GemmArgs& g, hipStream_t s) {

@@ -243,3 +243,42 @@ def test_router_topk_special_logits(mf, E):
     mf.memfine_router_fwd(s, t.from_numpy(X2).cuda().bfloat16(),
                           t.from_numpy(Wr2).cuda().bfloat16(), idx, gates)
     assert idx.cpu().numpy().tolist() == [[1, 0, 3, 4, 6, 7]] * 4
+
+
+# Router dX with the rows in registers (from 8192 tokens): a last row block of 1,
+# 244 and 255 rows, half a column block, a result larger than the cache, every reduction length, adding to dX;
+# the bits of the grouped GEMM (forced by a tile option).
+@pytest.mark.parametrize("T,E,h", [(8191, 256, 64), (8192, 64, 64), (8193, 128, 192),
+                                   (8436, 192, 320), (8447, 256, 448), (300001, 64, 512)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_router_dx_rows(mf, T, E, h, accumulate):
+    t = torch()
+    k = 4
+    log(f"router dX rows T={T} E={E} h={h} accumulate={accumulate}")
+    gen = t.Generator(device="cuda")
+    gen.manual_seed(T + E)
+    X = t.randn((T, h), generator=gen, device="cuda").bfloat16()
+    Wr = (t.randn((E, h), generator=gen, device="cuda") / 8).bfloat16()
+    idx = t.randn((T, E), generator=gen, device="cuda").topk(k, dim=1).indices.int().contiguous()
+    gates = t.softmax(t.randn((T, k), generator=gen, device="cuda"), 1)
+    dg = t.randn((T, k), generator=gen, device="cuda")
+    old = t.randn((T, h), generator=gen, device="cuda").bfloat16()
+    s = mf.make_shape(T, h, 64, E, k, mf.BF16)
+    got = []
+    for tile in (mf.TILE_AUTO, mf.TILE_256):
+        dX = old.clone() if accumulate else t.full((T, h), float("nan"), device="cuda").bfloat16()
+        dWr = t.empty((E, h), device="cuda")
+        try:
+            mf.memfine_set_launch_options(tile=tile)
+            mf.memfine_router_bwd(s, X, Wr, idx, gates, dg, dX, dWr, accumulate_dX=accumulate)
+        finally:
+            mf.memfine_set_launch_options()
+        got.append(dX)
+    assert t.equal(got[0], got[1])
+    if T > 100000:
+        return
+    g, d = gates.cpu().double(), dg.cpu().double()
+    dz = g * (d - (g * d).sum(1, keepdim=True))
+    D = t.zeros((T, E), dtype=t.float64).scatter_add_(1, idx.cpu().long(), dz)
+    ref = D @ Wr.cpu().double() + (old.cpu().double() if accumulate else 0)
+    assert relerr(host(got[0]), ref.numpy()) <= TOL["bf16"]
