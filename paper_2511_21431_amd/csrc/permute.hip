@@ -127,8 +127,24 @@ __global__ __launch_bounds__(1024) void scan_kernel(const int32_t* __restrict__ 
 
 // Exclusive scan over v[0..m) in place (one workgroup of 256 threads, m any
 // size): each thread scans a contiguous run, the run totals are scanned in
-// LDS, then each run is offset.  `part` is 256 ints of LDS.  Returns the total.
+// LDS, then each run is offset; up to 64 values one wave scans them in
+// registers.  `part` is 256 ints of LDS.  Returns the total.
 __device__ int32_t block_exclusive_scan(int32_t* v, int m, int32_t* part) {
+  if (m <= 64) {
+    const int lane = threadIdx.x & 63;
+    const int32_t x = lane < m ? v[lane] : 0;
+    int32_t inc = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t y = __shfl_up(inc, off);
+      if (lane >= off) inc += y;
+    }
+    const int32_t total = __shfl(inc, 63);
+    __syncthreads();  // every wave has read v
+    if ((int)threadIdx.x < m) v[threadIdx.x] = inc - x;
+    __syncthreads();
+    return total;
+  }
   const int tid = threadIdx.x, per = (m + 255) / 256;
   const int a = min(m, tid * per), b = min(m, a + per);
   int32_t sum = 0;
@@ -170,6 +186,13 @@ __device__ int32_t block_exclusive_scan(int32_t* v, int m, int32_t* part) {
 //   kSlots    the same from the slots themselves, which every workgroup
 //             reads: one launch in all.
 // `clear`: two ints that workgroup 0 sets to 0, or null.
+//
+// kCounts and workgroup 0's order are a chain of load latencies before the first
+// row is known, so `lanes` lanes share an expert's counts and comparisons and
+// eight of a lane's loads are in flight (a thread per count, with a division to
+// find its expert and an LDS add that 64 lanes sent to one address: 24576 slots,
+// 64 experts 17.8 us, now 9.3; 6000 slots, 64 experts 9.6, now 6.5; 16384 slots,
+// 16 experts 7.4, now 6.0).
 enum RowsFrom { kScanned, kCounts, kSlots };
 template <int kFrom>
 __global__ __launch_bounds__(256) void scatter_kernel(
@@ -189,9 +212,12 @@ __global__ __launch_bounds__(256) void scatter_kernel(
     int32_t* pre = wc + E;       // [E] the expert's slots in the workgroups before this one
     int32_t* cnt = wc + 2 * E;   // [E] the counts, kept for the order
     __shared__ int32_t spart[256];
-    for (int e = tid; e < E; e += 256) tot[e] = pre[e] = 0;
-    __syncthreads();
+    int lanes = 4;  // of one wave: a power of two, as many as 256 threads have per expert
+    while (lanes < 64 && 2 * lanes * E <= 256) lanes *= 2;
+    const int e0 = tid / lanes, es = 256 / lanes, l0 = tid & (lanes - 1);
     if constexpr (kFrom == kSlots) {
+      for (int e = tid; e < E; e += 256) tot[e] = pre[e] = 0;
+      __syncthreads();
       const int first = blockIdx.x * spb;
 #pragma unroll 4
       for (int i = tid; i < n; i += 256) {
@@ -202,13 +228,22 @@ __global__ __launch_bounds__(256) void scatter_kernel(
         }
       }
     } else {
-      const int64_t m = (int64_t)E * nb;
-      for (int64_t i = tid; i < m; i += 256) {
-        const int32_t v = bcount[i];
-        if (v) {
-          const int e = (int)(i / nb), b = (int)(i % nb);
-          atomicAdd(&tot[e], v);
-          if (b < (int)blockIdx.x) atomicAdd(&pre[e], v);
+      for (int e = e0; e < E; e += es) {
+        const int32_t* row = bcount + e * nb;  // E * nb <= 16384
+        int32_t all = 0, before = 0;
+#pragma unroll 8
+        for (int b = l0; b < nb; b += lanes) {
+          const int32_t v = row[b];
+          all += v;
+          before += b < (int)blockIdx.x ? v : 0;
+        }
+        for (int o = 1; o < lanes; o <<= 1) {
+          all += __shfl_xor(all, o);
+          before += __shfl_xor(before, o);
+        }
+        if (l0 == 0) {
+          tot[e] = all;
+          pre[e] = before;
         }
       }
     }
@@ -218,14 +253,21 @@ __global__ __launch_bounds__(256) void scatter_kernel(
     const int32_t total = block_exclusive_scan(tot, E, spart);
     for (int e = tid; e < E; e += 256) run[e] = tot[e] + pre[e];
     if (blockIdx.x == 0) {
-      for (int e = tid; e < E; e += 256) {
-        counts[e] = cnt[e];
-        offsets[e] = tot[e];
+      for (int e = e0; e < E; e += es) {
         // order: experts by descending count, ties by id
         const int32_t c = cnt[e];
         int rank = 0;
-        for (int e2 = 0; e2 < E; ++e2) rank += (cnt[e2] > c) || (cnt[e2] == c && e2 < e);
-        order[rank] = e;
+#pragma unroll 8
+        for (int e2 = l0; e2 < E; e2 += lanes) {
+          const int32_t c2 = cnt[e2];
+          rank += (c2 > c) || (c2 == c && e2 < e);
+        }
+        for (int o = 1; o < lanes; o <<= 1) rank += __shfl_xor(rank, o);
+        if (l0 == 0) {
+          counts[e] = c;
+          offsets[e] = tot[e];
+          order[rank] = e;
+        }
       }
       if (tid == 0) offsets[E] = total;
     }

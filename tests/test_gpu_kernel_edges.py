@@ -119,7 +119,8 @@ def test_f32_tile_shape_by_grid(mf, T):
 # workgroup up to 8192 slots: both sides of each line, dropped ids among them,
 # a chunk that starts inside the ids, and one expert taking every slot.
 @pytest.mark.parametrize("T,k,E", [(1, 1, 1), (512, 4, 256), (512, 4, 257), (683, 3, 9),
-                                   (1024, 8, 300), (2731, 3, 64), (4, 1, 1024)])
+                                   (1024, 8, 300), (2731, 3, 64), (4, 1, 1024),
+                                   (4096, 6, 64), (6000, 5, 65), (3000, 1, 1), (3000, 2, 5)])
 @pytest.mark.parametrize("hot", [False, True])
 def test_dispatch_and_count_lines(mf, T, k, E, hot):
     t = torch()
