@@ -423,7 +423,7 @@ const char* memfine_status_str(int status);
 #define MEMFINE_K_FC1_WGRAD   8
 #define MEMFINE_K_FC1_DGRAD   9
 #define MEMFINE_K_UNPERMUTE  10   /* dX sum over slots and gate gradient     */
-#define MEMFINE_K_FC1_BWD    11   /* FC1 dgrad and FC1 wgrad in one launch   */
+#define MEMFINE_K_FC1_BWD    11   /* FC1 dgrad with FC1 wgrad, or with both wgrads, in one launch */
 #define MEMFINE_K_ROUTER_FWD 12   /* router logits, softmax, top-k, gates    */
 #define MEMFINE_K_ROUTER_BWD_DX 13 /* router: dz per token, dX contribution */
 #define MEMFINE_K_ROUTER_WGRAD 14 /* router: split-K partials of dz^T X     */
