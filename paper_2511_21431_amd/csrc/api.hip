@@ -1289,7 +1289,6 @@ int memfine_router_bwd(const memfine_shape* shape, const void* d_X, const void* 
       g.W2 = d_Wr;
       g.ag = d_dX;
       g.accumulate = accumulate_dX;
-      g.T_h_bytes = T * (int64_t)EP * es;
       g.tile_override = opt.tile;
       g.raster = opt.raster;
       g.cus = device_cus();

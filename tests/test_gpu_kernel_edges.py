@@ -283,3 +283,56 @@ def test_router_dx_rows(mf, T, E, h, accumulate):
     D = t.zeros((T, E), dtype=t.float64).scatter_add_(1, idx.cpu().long(), dz)
     ref = D @ Wr.cpu().double() + (old.cpu().double() if accumulate else 0)
     assert relerr(host(got[0]), ref.numpy()) <= TOL["bf16"]
+
+
+# Router with more bytes of dz rows (E > h) or logits than 32-bit offsets reach:
+# T rows of 256 values, h = 64.  Rows sampled at the ends, around 2^31 and 2^32
+# bytes and at random against float64; bf16 dX as the grouped GEMM (forced by a
+# tile option) against the register-row kernel bit for bit.
+@pytest.mark.parametrize("T,dtype,accumulate", [(2097300, "f32", False), (4194400, "f32", True),
+                                                (4194400, "bf16", False), (8388650, "bf16", True)])
+def test_router_rows_past_32_bit_offsets(mf, T, dtype, accumulate):
+    t = torch()
+    E, h, k = 256, 64, 2
+    log(f"router rows past 32-bit offsets T={T} {dtype} accumulate={accumulate}")
+    dt = t.bfloat16 if dtype == "bf16" else t.float32
+    gen = t.Generator(device="cuda")
+    gen.manual_seed(T)
+    X = t.randn((T, h), generator=gen, device="cuda").to(dt)
+    Wr = (t.randn((E, h), generator=gen, device="cuda") / 8).to(dt)
+    dg = t.randn((T, k), generator=gen, device="cuda")
+    old = t.randn((T, h), generator=gen, device="cuda").to(dt)
+    s = mf.make_shape(T, h, 64, E, k, mf.BF16 if dtype == "bf16" else mf.F32)
+    idx = t.full((T, k), -1, dtype=t.int32, device="cuda")
+    gates, logits = t.empty((T, k), device="cuda"), t.full((T, E), float("nan"), device="cuda")
+    mf.memfine_router_fwd(s, X, Wr, idx, gates, logits)
+    per = 256 * (2 if dtype == "bf16" else 4)
+    rows = t.cat([t.arange(300), t.arange(T - 300, T), t.randint(0, T, (2000,))] +
+                 [t.arange(b // per - 300, min(b // per + 300, T)) for b in (1 << 31, 1 << 32)
+                  if b // per - 300 < T]).cuda()
+    z = X[rows].double() @ Wr.double().T
+    assert relerr(logits[rows].double().cpu().numpy(), z.cpu().numpy()) <= 1e-5
+    top = logits[rows].topk(k, dim=1)
+    assert t.equal(logits[rows].gather(1, idx[rows].long()), top.values)
+    del logits
+    got = []
+    for tile in (mf.TILE_AUTO, mf.TILE_256) if dtype == "bf16" else (mf.TILE_AUTO,):
+        dX = old.clone() if accumulate else t.full((T, h), float("nan"), device="cuda").to(dt)
+        dWr = t.full((E, h), float("nan"), device="cuda")
+        try:
+            mf.memfine_set_launch_options(tile=tile)
+            mf.memfine_router_bwd(s, X, Wr, idx, gates, dg, dX, dWr, accumulate_dX=accumulate)
+        finally:
+            mf.memfine_set_launch_options()
+        got.append(dX)
+    assert all(t.equal(got[0], g) for g in got)
+    g64, d64 = gates.double(), dg.double()
+    dz = g64 * (d64 - (g64 * d64).sum(1, keepdim=True))
+    D = t.zeros((len(rows), E), dtype=t.float64, device="cuda")
+    D.scatter_add_(1, idx[rows].long(), dz[rows])
+    ref = D @ Wr.double() + (old[rows].double() if accumulate else 0)
+    assert relerr(got[0][rows].double().cpu().numpy(), ref.cpu().numpy()) <= TOL[dtype]
+    ref = t.zeros((E, h), dtype=t.float64, device="cuda")
+    for j in range(k):
+        ref.index_add_(0, idx[:, j].long(), dz[:, j:j + 1] * X.double())
+    assert relerr(host(dWr), ref.cpu().numpy()) <= TOL[dtype]
