@@ -1083,15 +1083,13 @@ template <typename T, class C> struct ProbFC2Dgrad {
   }
   __host__ __device__ static int reduction(const GemmArgs& g) { return g.h; }
   __device__ __forceinline__ void init(const GemmArgs& g, const Tile& t, int wave, int lane) {
-    const int32_t* tok = g.tok_of_row;
+    A.rs = make_rsrc(g.dY, g.T_h_bytes);
+    const int32_t* tok = g.tok_of_row + t.m0;
     const uint32_t rowb = (uint32_t)g.h * sizeof(T);
-    if (tok == nullptr) {  // row m is token m: based at the tile, the rows may span any size
-      A.rs = make_rsrc(cptr<T>(g.dY, (int64_t)t.m0 * g.h), (int64_t)t.mrows * rowb);
-      A.init([&](int r) { return r < t.mrows ? (uint32_t)r * rowb : kOOB; }, wave, lane);
-    } else {
-      A.rs = make_rsrc(g.dY, g.T_h_bytes);
-      A.init([&](int r) { return r < t.mrows ? (uint32_t)tok[t.m0 + r] * rowb : kOOB; }, wave, lane);
-    }
+    A.init([&](int r) { return r < t.mrows ? (uint32_t)tok[r] * rowb : kOOB; }, wave, lane);
+    init_b(g, t, wave, lane);
+  }
+  __device__ __forceinline__ void init_b(const GemmArgs& g, const Tile& t, int wave, int lane) {
     const uint32_t ld = (uint32_t)g.F * sizeof(T);  // W2[e] row o holds F values
     B.rs = make_rsrc(cptr<T>(g.W2, (int64_t)t.e * g.h * g.F), (int64_t)g.h * ld);
 #pragma clang loop unroll(full)
@@ -1122,13 +1120,20 @@ template <typename T, class C> struct ProbFC2Dgrad {
 
 // Router backward's input gradient: dX[t, n] (+)= sum_e D[t, e] Wr[e, n],
 // with D the dense dz rows [T, E] (E % 64 == 0).  FC2 dgrad's problem with
-// one group of T rows: D in `dY` (K = E in GemmArgs.h, no `tok_of_row`), Wr in
+// one group of T rows: D in `dY` (K = E in GemmArgs.h; row m is token m), Wr in
 // `W2` (h columns in GemmArgs.F), dX in `ag`, overwritten or, with `accumulate`,
 // added to in fp32.
 template <typename T, class C> struct ProbRouterDx : ProbFC2Dgrad<T, C> {
   // reads dX when accumulating; the epilogue then has kStageSlabBytes of the
   // (idle) stages per wave
   static constexpr bool kEpilogueLoads = true;
+  // D's resource starts at the tile: T rows of E values pass 2^31 bytes where E > h
+  __device__ __forceinline__ void init(const GemmArgs& g, const Tile& t, int wave, int lane) {
+    const uint32_t rowb = (uint32_t)g.h * sizeof(T);
+    this->A.rs = make_rsrc(cptr<T>(g.dY, (int64_t)t.m0 * g.h), (int64_t)t.mrows * rowb);
+    this->A.init([&](int r) { return r < t.mrows ? (uint32_t)r * rowb : kOOB; }, wave, lane);
+    this->init_b(g, t, wave, lane);
+  }
   __device__ __forceinline__ void epilogue(const GemmArgs& g, const Tile& t, const Accum<C>& acc,
                                            int wm, int wn, int lane, char* slab) const {
     if (!g.accumulate) {

@@ -96,7 +96,7 @@ struct GemmArgs {
   int n, E, h, F;
   const int32_t* offsets;     // null: one group of all n rows (E = 1; not the weight gradients)
   const int32_t* order;
-  const int32_t* tok_of_row;  // null (FC2 dgrad only): row m is token m
+  const int32_t* tok_of_row;
   const float* gate_of_row;
   const void* X;     // [T, h]
   const void* dY;    // [T, h]
