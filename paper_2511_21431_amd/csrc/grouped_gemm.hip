@@ -1513,28 +1513,31 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
     const int m0 = __builtin_amdgcn_readfirstlane(t.m0);
     const int mrows = __builtin_amdgcn_readfirstlane(t.mrows);
     const int n0 = __builtin_amdgcn_readfirstlane(t.n0);
-    const __amdgpu_buffer_rsrc_t rs =
-        make_rsrc((kFC1 ? g.dW1 : g.dW2) + (int64_t)e * M(g) * Nn + (int64_t)m0 * Nn,
-                  (int64_t)mrows * rowb);
     const bool add = acc_of(t);
     constexpr int U = C::MB * C::NB, D = U < 3 ? U : 3;  // blocks; blocks of old values in flight
-    // Access q of block u: lane l has 16 bytes at unit l % 8 of row 8 q + l / 8.
-    // The lane's offset is fixed, block and row group go in the scalar offset.
+    // A block's resource starts at its first element (a tile of 256 rows may
+    // span 2^32 bytes, 32 rows of at most 2^25 bytes do not: the shape check
+    // bounds N by 2^23).  Access q of a block: lane l has 16 bytes at unit l % 8 of
+    // row 8 q + l / 8; the lane's offset is fixed, the row group goes in the
+    // scalar offset, below the range for masked blocks too.
+    float* dW = (kFC1 ? g.dW1 : g.dW2) +
+                ((int64_t)e * M(g) + m0 + wm * C::WTM) * (int64_t)Nn + n0 + wn * C::WTN;
     const uint32_t lane_off = (uint32_t)(lane >> 3) * rowb + (uint32_t)(lane & 7) * 16;
+    auto rsrc = [&](int u) {
+      return make_rsrc32(dW + (int64_t)(u / C::NB * 32) * Nn + u % C::NB * 32, 32 * rowb);
+    };
     auto voff = [&](int u) {
       const int mb = u / C::NB, nb = u % C::NB;
       return wm * C::WTM + mb * 32 < mrows && n0 + wn * C::WTN + nb * 32 < Nn ? lane_off : kOOB;
     };
-    auto soff = [&](int u, int q) {
-      return (uint32_t)(wm * C::WTM + (u / C::NB) * 32 + 8 * q) * rowb +
-             (uint32_t)(n0 + wn * C::WTN + (u % C::NB) * 32) * 4;
-    };
+    auto soff = [&](int q) { return (uint32_t)(8 * q) * rowb; };
     u32x4_t old[D][4];
     auto fetch = [&](int u) {
       const uint32_t vo = voff(u);
+      const __amdgpu_buffer_rsrc_t rs = rsrc(u);
 #pragma clang loop unroll(full)
       for (int q = 0; q < 4; ++q)
-        old[u % D][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, soff(u, q), kNonTemporal);
+        old[u % D][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, soff(q), kNonTemporal);
     };
     const int wr = (lane & 31) * 128 + (((lane >> 5) ^ (lane & 7)) << 4);
     const int rd = (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) << 4);
@@ -1547,6 +1550,7 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
       }
       asm volatile("" ::: "memory");  // the writes above before the reads below
       const uint32_t vo = voff(u);
+      const __amdgpu_buffer_rsrc_t rs = rsrc(u);
 #pragma clang loop unroll(full)
       for (int q = 0; q < 4; ++q) {
         f32x4_t x = *(const f32x4_t*)(slab + rd + q * 1024);
@@ -1555,7 +1559,7 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
 #pragma clang loop unroll(full)
           for (int c = 0; c < 4; ++c) x[c] += o[c];
         }
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), rs, vo, soff(u, q),
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), rs, vo, soff(q),
                                                kNonTemporal);
       }
       asm volatile("" ::: "memory");  // the reads above before the next writes

@@ -336,3 +336,46 @@ def test_router_rows_past_32_bit_offsets(mf, T, dtype, accumulate):
     for j in range(k):
         ref.index_add_(0, idx[:, j].long(), dz[:, j:j + 1] * X.double())
     assert relerr(host(dWr), ref.cpu().numpy()) <= TOL[dtype]
+
+
+# Weight gradients of an expert whose tile of 256 rows spans more than 2^31
+# bytes (dW1: 256 rows of 2228224) or would if all of its rows were there (dW2: 64),
+# against float64 on the GPU.
+@pytest.mark.parametrize("h,F", [(64, 2228224), (2228224, 128)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_wgrad_of_very_long_rows(mf, h, F, accumulate):
+    t = torch()
+    T = 5
+    log(f"wgrad long rows h={h} F={F} accumulate={accumulate}")
+    gen = t.Generator(device="cuda")
+    gen.manual_seed(h)
+
+    def rand(*shape, scale=1.0, dtype=t.bfloat16):
+        return (t.randn(shape, generator=gen, device="cuda") * scale).to(dtype)
+    X, dY = rand(T, h), rand(T, h)
+    W1, W2 = rand(1, 2 * F, h, scale=h ** -0.5), rand(1, h, F, scale=h ** -0.5)
+    idx = t.zeros((T, 1), dtype=t.int32, device="cuda")
+    gates = t.rand((T, 1), generator=gen, device="cuda") + 0.5
+    dX, dg = t.full((T, h), float("nan"), device="cuda").bfloat16(), t.empty((T, 1), device="cuda")
+    if accumulate:
+        dW = [rand(*W.shape, dtype=t.float32) for W in (W1, W2)]
+    else:
+        dW = [t.full(W.shape, float("nan"), device="cuda") for W in (W1, W2)]
+    old = [x[0].clone() if accumulate else 0 for x in dW]
+    mf.memfine_moe_bwd(mf.make_shape(T, h, F, 1, 1, mf.BF16), 1, X, idx, gates, W1, W2, dY, dX, *dW,
+                       dg, accumulate_dW=accumulate)
+    x, y, g = X.double(), dY.double(), gates.double()
+    u = x @ W1[0].double().T
+    gate, up = u[:, :F], u[:, F:]
+    s = t.sigmoid(gate)
+    a, dA = gate * s * up, y @ W2[0].double()
+    du = t.cat((g * dA * up * s * (1 + gate * (1 - s)), g * dA * gate * s), 1)
+
+    def check(name, got, ref):
+        err = float((got.double() - ref).abs().max() / ref.abs().max())
+        log(f"  {name} {err:.2e}")
+        assert err <= TOL["bf16"], name
+    check("dgates", dg, (dA * a).sum(1, keepdim=True))
+    check("dX", dX, du @ W1[0].double())
+    check("dW2", dW[1][0], (g * y).T @ a + old[1])
+    check("dW1", dW[0][0], du.T @ x + old[0])
