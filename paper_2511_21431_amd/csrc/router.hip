@@ -381,6 +381,9 @@ __global__ __launch_bounds__(256) void router_dz_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ gates,
     const float* __restrict__ dgates, int64_t T_, int E, int k, int EP, T* __restrict__ D,
     RouterSplit sp) {
+  // products and sums round one by one, as where the products move between lanes
+  // (router_bwd_dx_kernel): both kernels give the same dz
+#pragma clang fp contract(off)
   extern __shared__ u32x4_t rows16[];  // kDzTokens rows of EP elements
   T* rows = (T*)rows16;
   const int64_t t0 = (int64_t)blockIdx.x * kDzTokens;

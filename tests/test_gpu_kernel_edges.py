@@ -379,3 +379,49 @@ def test_wgrad_of_very_long_rows(mf, h, F, accumulate):
     check("dX", dX, du @ W1[0].double())
     check("dW2", dW[1][0], (g * y).T @ a + old[1])
     check("dW1", dW[0][0], du.T @ x + old[0])
+
+
+# Router dz rows where dX is a product from them (E a multiple of 64): with Wr the
+# identity dX is dz itself, so the bits are those of fp32 arithmetic with the sum
+# over the slots as a pairwise tree of 16 - in fp32, with up to 64 KB of rows per
+# workgroup, and rounded to bf16, below and from 8192 tokens.  Some ids are out
+# of range (dropped) or repeated (added, in slot order).
+@pytest.mark.parametrize("T,E,k,dtype", [(70, 64, 5, "f32"), (1, 128, 16, "f32"),
+                                         (333, 192, 8, "f32"), (8200, 256, 8, "f32"),
+                                         (129, 256, 16, "bf16"), (8200, 128, 3, "bf16")])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_router_dz_rows(mf, T, E, k, dtype, accumulate):
+    t = torch()
+    log(f"router dz rows T={T} E={E} k={k} {dtype} accumulate={accumulate}")
+    rng = np.random.default_rng(T + E)
+    f = np.float32
+    idx = rng.permuted(np.tile(np.arange(E), (T, 1)), axis=1)[:, :k].astype(np.int32)
+    idx[::3, 0] = np.array([E, -1, E + 7])[np.arange(T)[::3] % 3]
+    idx[1::4, -1] = idx[1::4, 1]
+    g = rng.random((T, k)).astype(f)
+    d = rng.standard_normal((T, k)).astype(f)
+    old = mw.round_to_bf16(rng.standard_normal((T, E))).astype(f)
+    ok = (idx >= 0) & (idx < E)
+    gk, dk = (np.zeros((T, 16), f) for _ in range(2))
+    gk[:, :k], dk[:, :k] = np.where(ok, g, 0), np.where(ok, d, 0)
+    s = gk * dk
+    while s.shape[1] > 1:
+        s = s[:, 0::2] + s[:, 1::2]
+    dz = gk * (dk - s)
+    ref = np.zeros((T, E), f)
+    for j in range(k):
+        rows = np.flatnonzero(ok[:, j])
+        ref[rows, idx[rows, j]] += dz[rows, j]
+    rnd = (lambda x: x) if dtype == "f32" else (lambda x: mw.round_to_bf16(x).astype(f))
+    ref = rnd(ref)
+    if accumulate:
+        ref = rnd(old + ref)
+    dt = t.float32 if dtype == "f32" else t.bfloat16
+    dev = [t.from_numpy(a).cuda() for a in (idx, g, d)]
+    Wr = t.eye(E, device="cuda", dtype=dt)
+    X = t.from_numpy(old).cuda().to(dt)
+    dX = X.clone() if accumulate else t.full((T, E), float("nan"), device="cuda").to(dt)
+    dWr = t.empty((E, E), device="cuda")
+    shape = mf.make_shape(T, E, 64, E, k, mf.F32 if dtype == "f32" else mf.BF16)
+    mf.memfine_router_bwd(shape, X, Wr, *dev, dX, dWr, accumulate_dX=accumulate)
+    assert np.array_equal(host(dX), ref)
