@@ -347,6 +347,7 @@ GemmArgs gemm_args(const memfine_shape& s, int64_t n, const ChunkBuffers& c,
   g.dtype = s.dtype;
   g.n = (int)n;
   g.E = s.E;
+  g.groups = s.E;
   g.h = s.h;
   g.F = s.F;
   g.offsets = c.m.offsets;
@@ -449,6 +450,10 @@ int64_t expert_chunks(const memfine_shape& s, int32_t chunks) {
 }
 int64_t expert_chunk_row(const memfine_shape& s, int64_t C, int64_t c) {
   return c * (s.T * (int64_t)s.k) / C;
+}
+// experts whose rows fill one of C expert-ordered chunks, for balanced loads
+int expert_chunk_groups(const memfine_shape& s, int64_t C) {
+  return (int)std::max<int64_t>(1, s.E / C);
 }
 
 int64_t workspace_bytes(const memfine_shape& s, int32_t chunks, int32_t pass, int32_t order) {
@@ -815,6 +820,7 @@ int moe_fwd_experts(const memfine_shape& S, int32_t chunks, const void* d_X, con
     err = launch_chunk_view(mb.m.offsets, S.E, (int)p0, (int)p1, c == 0, 0, mb.off_c, mb.order_c,
                             mb.wexp, mb.wmode, nullptr, s);
     GemmArgs g = gemm_args(S, n, cb, opt);
+    g.groups = expert_chunk_groups(S, C);
     g.offsets = mb.off_c;
     g.order = mb.order_c;
     g.tok_of_row = mb.m.tok_of_row + p0;
@@ -1053,6 +1059,7 @@ int moe_bwd_experts(const memfine_shape& S, int32_t chunks, const void* d_X, con
     err = launch_chunk_view(mb.m.offsets, S.E, (int)p0, (int)p1, c == 0, accumulate_dW, mb.off_c,
                             mb.order_c, mb.wexp, mb.wmode, cb.ctr, s);
     GemmArgs g = gemm_args(S, n, cb, opt);
+    g.groups = expert_chunk_groups(S, C);
     g.offsets = mb.off_c;
     g.order = mb.order_c;
     g.tok_of_row = mb.m.tok_of_row + p0;
@@ -1208,7 +1215,7 @@ int memfine_router_fwd(const memfine_shape* shape, const void* d_X, const void* 
     GemmArgs g = {};
     g.dtype = S.dtype;
     g.n = (int)S.T;
-    g.E = 1;
+    g.E = g.groups = 1;
     g.h = S.E;   // output columns: the logits
     g.F = S.h;   // reduction: the hidden size
     g.a = const_cast<void*>(d_X);
@@ -1282,7 +1289,7 @@ int memfine_router_bwd(const memfine_shape* shape, const void* d_X, const void* 
       GemmArgs g = {};
       g.dtype = S.dtype;
       g.n = (int)T;
-      g.E = 1;
+      g.E = g.groups = 1;
       g.h = EP;    // reduction: the dense dz row
       g.F = S.h;   // output columns: the hidden size
       g.dY = D;
@@ -1302,7 +1309,7 @@ int memfine_router_bwd(const memfine_shape* shape, const void* d_X, const void* 
     GemmArgs g = {};
     g.dtype = S.dtype;
     g.n = (int)T;
-    g.E = splits;
+    g.E = g.groups = splits;
     g.h = S.h;
     g.F = EP / 2;
     g.offsets = offsets;

@@ -2319,22 +2319,50 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
 
 // Pick the tile shape.  Whatever is picked, an element is the same sum.
 //
-// bf16, row-grouped problems (by n / E, the rows of an average expert; the
-// host does not know the counts).  Measured at 32 experts, h 2048, F 1408,
-// Dirichlet loads, us for FC1 / FC2 / FC2 dgrad / recompute / FC1 dgrad:
-//   rows   256 x 256               128 x 128 walk          Thin walk
-//     16   112/ 44/ 38/142/121      81/ 39/ 32/106/123      73/ 40/ 36/ 92/135
-//     32   113/ 45/ 39/146/118      84/ 41/ 33/109/120      74/ 47/ 36/ 92/128
-//     64   118/ 51/ 45/150/140      84/ 58/ 35/108/151      89/ 48/ 47/101/138
-//    128   122/ 70/ 49/152/171     115/ 64/ 57/132/146     113/ 67/ 56/124/155
-//    256   150/ 92/ 79/173/200     153/ 86/ 72/174/189     179/104/ 94/196/230
-//    512   231/130/114/265/261     246/137/129/281/281     293/173/159/319/372
-// and at 4 rows, h 7168, F 2048: 354/257/179/368/453, 316/207/165/323/394,
-// 315/184/172/318/390 (FC1 there reads 1.88 GB: 0.36 ms at the copy rate).
-// Few rows per expert leave the weight tiles as the traffic: they want many
-// small tiles over the CUs and bytes in flight (Thin: 32 KB of weights per
-// workgroup ahead); many rows want operand reuse (256 x 256, one per CU).
-constexpr int kThinRows = 48, kMidRows = 320;
+// bf16, row-grouped problems, by the rows of an average expert (the host does
+// not know the counts) and by the 256 x 256 tiles these make.  Few rows per
+// expert leave the weight tiles as the traffic: they want many small tiles over the
+// CUs and bytes in flight (Thin: 32 KB of weights per workgroup ahead).
+// Many rows want operand reuse (256 x 256, one per CU) unless those tiles
+// leave CUs idle.  Measured us, Thin / 128 x 128 / 256 x 256, balanced loads
+// and, after the semicolon, Dirichlet(2) loads:
+//   experts, h, F    rows   FC1 (352, 128, 768 big tiles)   FC2 (256, 224, 512)
+//   32, 2048, 1408     32    85/ 99/126;  94/ 98/128         38/ 37/ 42;  46/ 54/ 44
+//                      64    87/101/131;  99/101/133         41/ 40/ 44;  46/ 59/ 45
+//                     160   130/121/137; 132/124/124         68/ 62/ 53;  71/ 64/ 69
+//                     256   167/139/151; 177/156/153         94/ 72/ 60;  97/ 81/ 87
+//   8, 7168, 2048      64    90/119/208; 123/119/208         60/ 62/ 64;  65/ 63/ 64
+//                     192   165/148/215; 211/145/179         98/ 83/ 71; 103/ 85/ 97
+//   128, 1024, 768     16   130/152/141; 130/152/141         78/ 88/ 90;  79/ 88/ 90
+//                      32   132/152/144; 155/153/146         80/ 88/ 91; 106/ 88/ 91
+//                      64   137/157/150; 198/183/153         85/ 90/ 94; 135/117/ 94
+//                     192   332/284/175; 379/315/206        215/167/107; 246/196/140
+// With more than 64 experts a tile is found by walking them, which small
+// tiles pay more often: Thin ends at kThinRowsWalked there.
+//
+// Past Thin, 256 x 256 where their last round is nearly full (kFull; they
+// then also ride out skew, which adds small tiles first) and from kBigRows where they
+// give more than half of the CUs one (128 tiles on 256 CUs lose: 16, 1024, 4096 at 320
+// rows FC2 118 against 71; 140 tiles win: 20, 1600, 960 at 160 rows 26
+// against 30).  Over 890 points like these (five problems, seven layers, 16 to 768
+// rows) this takes 0.916 of the time of 256 x 256 tiles throughout; 8 of them are
+// slower by more than 10 %, the worst by 25 % (128, 1024, 768, FC2 dgrad at 128
+// skewed rows).  Chosen by rows alone (48 and 320): 0.940, 102 of them slower by more
+// than 10 %, forward calls by up to 1.6 times (128 experts, 160 rows).
+constexpr int kThinRows = 48, kThinRowsWalked = 16, kBigRows = 160;
+constexpr int kFull = 85;  // percent of the CUs
+enum RowTile { kThinTile, kSmallTile, kBigTile };
+inline int64_t rows_per_group(const GemmArgs& g) { return ((int64_t)g.n + g.groups - 1) / g.groups; }
+template <class P> RowTile row_tile(const GemmArgs& g) {  // P: a problem on 256 x 256 tiles
+  const int64_t rows = rows_per_group(g);
+  if (rows <= (g.E <= 64 ? kThinRows : kThinRowsWalked)) return kThinTile;
+  // m-tiles of an average expert in quarters, with a quarter more for uneven loads
+  const int64_t mt4 = std::max<int64_t>(4, (rows + 63) / 64 + 1);
+  const int64_t tiles = g.groups * mt4 * ((P::ncols(g) + P::BNU - 1) / P::BNU) / 4;
+  const int64_t rounds = (tiles + g.cus - 1) / g.cus;
+  if (100 * tiles >= kFull * rounds * g.cus) return kBigTile;
+  return rows >= kBigRows && 2 * tiles > g.cus ? kBigTile : kSmallTile;
+}
 // The weight gradients (K = an expert's rows) take 256 x 256 tiles from 640 of
 // them (2.5 rounds of the CUs): below, the launch lasts as long as the tiles
 // of the expert with most rows, and 128 x 128 tiles spread them over four
@@ -2372,16 +2400,22 @@ hipError_t launch_auto(const GemmArgs& g_in, hipStream_t s) {
     default: break;
   }
   if constexpr (Any::kEqualTiles) {  // row-grouped
-    if (g.n <= (int64_t)kThinRows * g.E) return launch_walk<bf16_t, PT, Thin>(g, s);
-    if (g.n < (int64_t)kMidRows * g.E) return launch_walk<bf16_t, PT, Small>(g, s);
+    const RowTile tile = row_tile<Any>(g);
+    if (tile == kThinTile) return launch_walk<bf16_t, PT, Thin>(g, s);
+    if (tile == kSmallTile) {
+      // (tiles that are all resident have no walk to make: 8 experts, h = F =
+      // 1024, 64 rows, FC2 15.4 us walking, 14.7 us one tile per workgroup)
+      if (PT<bf16_t, Small>::grid(g) <= g.cus * Small::kWgPerCu)
+        return launch_tiles<bf16_t, PT, Small>(g, s);
+      return launch_walk<bf16_t, PT, Small>(g, s);
+    }
+  } else {
+    // (tile_ctr: the layer's weight gradients; the router's have equal row ranges)
+    const int least = g.tile_ctr != nullptr ? kWgradGrid : 128;
+    if (Any::grid(g) < least) return launch_tiles<bf16_t, PT, Small>(g, s);
   }
-  // (tile_ctr: the layer's weight gradients; the router's have equal row ranges)
-  const int least = !Any::kEqualTiles && g.tile_ctr != nullptr ? kWgradGrid : 128;
-  if (Any::grid(g) >= least) {
-    if (g.split_tail) return launch_split_cfg<PT, Big8, Quarter8>(g, s);
-    return launch_tiles<bf16_t, PT, Big8>(g, s);
-  }
-  return launch_tiles<bf16_t, PT, Small>(g, s);
+  if (g.split_tail) return launch_split_cfg<PT, Big8, Quarter8>(g, s);
+  return launch_tiles<bf16_t, PT, Big8>(g, s);
 }
 
 template <template <typename, class> class P1, template <typename, class> class P2>
@@ -2399,13 +2433,15 @@ hipError_t launch_pair(const GemmArgs& g_in, hipStream_t s) {
 // The three products that read what the recomputation wrote, as one launch
 // where each alone takes the small tiles because it would leave CUs idle: one
 // launch's last round and latency instead of three.
+constexpr int kMergeRows = 320;
 bool bwd_merges(const GemmArgs& g) {
   if (g.tile_override != MEMFINE_TILE_AUTO) return false;
   if (g.dtype != 0)
     return ProbFC1Dgrad<float, Small>::grid(g) < kF32SmallGrid &&
            FC1W<float, Small>::grid(g) < kF32SmallGrid && FC2W<float, Small>::grid(g) < kF32SmallGrid;
-  return g.n < (int64_t)kMidRows * g.E && FC1W<float, Big8>::grid(g) < kWgradGrid &&
-         FC2W<float, Big8>::grid(g) < kWgradGrid;
+  return rows_per_group(g) < kMergeRows &&
+         row_tile<ProbFC1Dgrad<float, Big8>>(g) != kBigTile &&
+         FC1W<float, Big8>::grid(g) < kWgradGrid && FC2W<float, Big8>::grid(g) < kWgradGrid;
 }
 hipError_t launch_bwd_merged(const GemmArgs& g_in, hipStream_t s) {
   GemmArgs g = g_in;

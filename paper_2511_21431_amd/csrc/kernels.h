@@ -94,6 +94,7 @@ hipError_t launch_unpermute_rows(int dtype, const void* dxp, const float* dgp, i
 struct GemmArgs {
   int dtype;
   int n, E, h, F;
+  int groups;                 // experts that the rows are spread over, about (tile shapes)
   const int32_t* offsets;     // null: one group of all n rows (E = 1; not the weight gradients)
   const int32_t* order;
   const int32_t* tok_of_row;

@@ -90,6 +90,19 @@ def test_tile_shape_by_rows(mf, T, E, h, F):
             assert np.array_equal(other[key], B[key]), (tile, key)
 
 
+# The same with enough experts for the other lines of the rule: 16 rows per expert
+# past 64 experts, 160 rows with 160 tiles of 256 x 256 (FC2 and FC1 dgrad, 80 experts x
+# 2) and with 80 (FC1, FC2 dgrad), a nearly full last round (240 tiles, 60 rows); and
+# expert-ordered chunks, whose rows come from a few of the experts.
+@pytest.mark.parametrize("T,E,h,F", [(640, 80, 320, 64), (641, 80, 320, 64), (6360, 80, 320, 128),
+                                     (6361, 80, 320, 128), (2400, 80, 576, 64),
+                                     (2560, 32, 320, 192)])
+def test_tile_shape_by_rows_and_grid(mf, T, E, h, F):
+    test_tile_shape_by_rows(mf, T, E, h, F)
+    w = mw.Workload("rows", T=T, h=h, F=F, E=E, k=2, dtype="bf16", routing="dirichlet")
+    _check_bwd(mf, w, 900 + T, 5, True, chunk_order=mf.CHUNK_EXPERTS)
+
+
 # Weight gradients: 128 x 128 tiles below a grid of 640 tiles of 256 x 256 (here
 # one per expert), the larger ones from there; most experts have no row.
 @pytest.mark.parametrize("E", [639, 640])
