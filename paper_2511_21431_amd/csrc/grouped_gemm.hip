@@ -2363,14 +2363,31 @@ template <class P> RowTile row_tile(const GemmArgs& g) {  // P: a problem on 256
   if (100 * tiles >= kFull * rounds * g.cus) return kBigTile;
   return rows >= kBigRows && 2 * tiles > g.cus ? kBigTile : kSmallTile;
 }
-// The weight gradients (K = an expert's rows) take 256 x 256 tiles from 640 of
-// them (2.5 rounds of the CUs): below, the launch lasts as long as the tiles
-// of the expert with most rows, and 128 x 128 tiles spread them over four
-// times the workgroups.  Measured, 256 x 256 against 128 x 128: 256 tiles (32
-// experts, 512 x 1024, 1500 rows) 186 / 110 us, 512 tiles (8, 1024 x 4096,
-// 1000 rows) 120 / 98, 560 (20, 1600 x 960, 375 rows) 70 / 51, 768 (16, 2048
-// x 1408, 512 rows) 82 / 92, 1024 (8, 8192 x 1024, 1000 rows) 184 / 231.
-constexpr int kWgradGrid = 640;
+// The weight gradients (K = an expert's rows) take 256 x 256 tiles from
+// kWgradGrid (2.5 rounds of the CUs) of them.  Below, a launch lasts as long as the tiles of
+// the expert with most rows, and 128 x 128 tiles spread them over four times the
+// workgroups; but they read twice as much per product, and where the
+// rows are many and the loads even, that decides: 256 x 256 then from kWgradRound tiles
+// (1.75 rounds) with kWgradRowsRound rows per expert, and from kWgradPart tiles with
+// kWgradRowsPart rows.  Time of 128 x 128 over that of 256 x 256, overwriting
+// dW, balanced / Dirichlet(5) / Dirichlet(1) loads:
+//   tiles (experts, h, F)         384 rows     1000 rows    2048 rows    4096 rows   16384 rows
+//    128 FC1 (8, 1024,  512)   .87 .79 .83  .93 .87 .92  .94 .89 .82  .93 .82 .87   .81 .80 .71
+//    192 FC1 (8, 1024,  768)   .93 .90 .64 1.06 .89 .78 1.07 .80 .74 1.21 .82 .96  1.25 .79 .90
+//    256 FC1 (8, 1024, 1024)   .74 .73 .63  .80 .77 .84  .83 .72 .82 1.41 .92 1.0  1.43 .82 1.05
+//    256 FC2 (64, 512,  512)   .73 .79 .65 1.14 .87 .75 1.35 .95 .79 1.38 1.2 .74
+//    384 FC1 (24, 512, 1024)   .79 .84 .72  .88 .85 .70 1.09 .92 .90 1.11 1.0 .72
+//    448 FC1 (8, 1024, 1792)  1.02 1.0 .84 1.12 1.1 .97 1.23 1.0 .90 1.28 1.0 1.2  1.36 1.1 1.10
+//    512 FC1 (8, 1024, 2048)  1.06 1.1 .91 1.18 1.1 .98 1.33 1.1 .97 1.40 1.1 1.2  1.45 1.2 1.04
+//    560 FC2 (20, 1600, 960)   .96 1.1 .93 1.07 1.0 .77 1.13 1.0 .69 1.18 .98 .66  1.19 1.1 .92
+//   1120 FC1 (20, 1600, 960)  1.13 1.2 1.2 1.16 1.3 1.2 1.20 1.3 1.2 1.32 1.4 .98  1.49 1.6 1.65
+constexpr int kWgradGrid = 640, kWgradRound = 448, kWgradRowsRound = 640;
+constexpr int kWgradPart = 160, kWgradRowsPart = 2048;
+template <class P> bool wgrad_big(const GemmArgs& g) {  // P: a problem on 256 x 256 tiles
+  const int64_t tiles = P::grid(g), rows = rows_per_group(g);
+  return tiles >= kWgradGrid || (tiles >= kWgradRound && rows >= kWgradRowsRound) ||
+         (tiles >= kWgradPart && rows >= kWgradRowsPart);
+}
 //
 // fp32: 64-row tiles up to kF32SmallGrid 128 x 128 tiles (2.5 rounds of the
 // 512 that are resident): 36 m-tiles x 8 (FC1 dgrad at 4096 slots, h 1024, F
@@ -2411,8 +2428,8 @@ hipError_t launch_auto(const GemmArgs& g_in, hipStream_t s) {
     }
   } else {
     // (tile_ctr: the layer's weight gradients; the router's have equal row ranges)
-    const int least = g.tile_ctr != nullptr ? kWgradGrid : 128;
-    if (Any::grid(g) < least) return launch_tiles<bf16_t, PT, Small>(g, s);
+    if (g.tile_ctr != nullptr ? !wgrad_big<Any>(g) : Any::grid(g) < 128)
+      return launch_tiles<bf16_t, PT, Small>(g, s);
   }
   if (g.split_tail) return launch_split_cfg<PT, Big8, Quarter8>(g, s);
   return launch_tiles<bf16_t, PT, Big8>(g, s);
@@ -2441,7 +2458,7 @@ bool bwd_merges(const GemmArgs& g) {
            FC1W<float, Small>::grid(g) < kF32SmallGrid && FC2W<float, Small>::grid(g) < kF32SmallGrid;
   return rows_per_group(g) < kMergeRows &&
          row_tile<ProbFC1Dgrad<float, Big8>>(g) != kBigTile &&
-         FC1W<float, Big8>::grid(g) < kWgradGrid && FC2W<float, Big8>::grid(g) < kWgradGrid;
+         !wgrad_big<FC1W<float, Big8>>(g) && !wgrad_big<FC2W<float, Big8>>(g);
 }
 hipError_t launch_bwd_merged(const GemmArgs& g_in, hipStream_t s) {
   GemmArgs g = g_in;

@@ -114,6 +114,40 @@ def test_wgrad_tile_shape_by_grid(mf, E):
         _check_bwd(mf, w, 70 + E, 2, accumulate)
 
 
+# The rows at which fewer tiles of 256 x 256 take the larger shape: from 448 of
+# them (512 here, FC1 wgrad) 640 rows per expert, from 160 (192, FC2 wgrad of the
+# second) 2048; with a tile option forcing the other shape the bits are the same.
+@pytest.mark.parametrize("T,E,h,F", [(5119, 16, 512, 2048), (5120, 16, 512, 2048),
+                                     (2047, 2, 2048, 3072), (2048, 2, 2048, 3072)])
+def test_wgrad_tile_shape_by_rows(mf, T, E, h, F):
+    w = mw.Workload("wrows", T=T, h=h, F=F, E=E, k=2, dtype="bf16", routing="dirichlet")
+    log(f"wgrad tile shape T={T} E={E} h={h} F={F}")
+    t = torch()
+    rng = np.random.default_rng(T)
+    dev = {"X": t.randn((T, h), device="cuda").bfloat16(), "dY": t.randn((T, h), device="cuda").bfloat16(),
+           "W1": (t.randn((E, 2 * F, h), device="cuda") / 16).bfloat16(),
+           "W2": (t.randn((E, h, F), device="cuda") / 16).bfloat16(),
+           "idx": t.from_numpy(rng.integers(0, E, (T, 2)).astype(np.int32)).cuda(),
+           "gates": t.rand((T, 2), device="cuda")}
+    got = []
+    for tile in (mf.TILE_AUTO, mf.TILE_128, mf.TILE_256):
+        try:
+            mf.memfine_set_launch_options(tile=tile)
+            got.append(run_bwd(w, dev, 1))
+        finally:
+            mf.memfine_set_launch_options()
+    for key in got[0]:
+        assert t.equal(got[0][key], got[1][key]) and t.equal(got[0][key], got[2][key]), key
+    # dW2 = (gate * dY)^T a, by expert in float64
+    x, y, g = dev["X"].double(), dev["dY"].double(), dev["gates"].double()
+    e = E - 1
+    tok, slot = (dev["idx"] == e).nonzero(as_tuple=True)
+    u = x[tok] @ dev["W1"][e].double().T
+    a = t.nn.functional.silu(u[:, :F]) * u[:, F:]
+    ref = (g[tok, slot][:, None] * y[tok]).T @ a
+    assert float((got[0]["dW2"][e].double() - ref).abs().max() / ref.abs().max()) <= TOL["bf16"]
+
+
 # fp32: 64-row tiles below 1280 tiles of 128 x 128, the larger ones from there
 # (FC1: F / 64 = 256 column tiles x 4 and x 5 row tiles).
 @pytest.mark.parametrize("T", [512, 640])
