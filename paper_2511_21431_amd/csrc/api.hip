@@ -1202,8 +1202,8 @@ int memfine_router_fwd(const memfine_shape* shape, const void* d_X, const void* 
                      (d_logits ? 4.0 * Td * S.E : 0.0));
   if (S.E <= 64 || S.E % 32 != 0)
     return hip_status(launch_router_fwd(S.dtype, d_X, d_Wr, S.T, S.h, S.E, S.k, d_idx, d_gates,
-                                        d_logits, s));
-  // Wide routers: the logits as a grouped GEMM on 256-token tiles (each tile
+                                        d_logits, device_cus(), s));
+  // Wide routers: the logits as a grouped GEMM (each tile of 64 to 256 tokens
   // reads Wr once; one fused kernel per 32 tokens read it T / 32 times), then
   // their top-k.  Working memory: without d_logits, the logits themselves.
   const size_t lg_bytes = d_logits ? 0 : (size_t)(S.T * (int64_t)S.E * 4);

@@ -130,7 +130,8 @@ int dgate_partials(int F);
 // Router (E <= 256 experts, k <= 16): logits on the matrix cores, softmax,
 // top-k and renormalised gates; logits may be null.
 hipError_t launch_router_fwd(int dtype, const void* X, const void* Wr, int64_t T, int h, int E,
-                             int k, int32_t* idx, float* gates, float* logits, hipStream_t s);
+                             int k, int32_t* idx, float* gates, float* logits, int cus,
+                             hipStream_t s);
 // Router forward in two steps for wide routers: the logits [T, E] (fp32) as a
 // grouped GEMM (launch_router_logits: one group of T rows, no offsets; X in a,
 // K = h in F, Wr in W2, E in h, logits in y), then their top-k

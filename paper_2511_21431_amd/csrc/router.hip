@@ -52,13 +52,13 @@ template <> struct RK<float> {
 
 // Forward.  A workgroup owns 32 tokens x 32 NB experts (NB = 1 or 2); its
 // four waves take interleaved K blocks (wave w: blocks w, w + 4, ...) with the
-// operands loaded straight into registers one block ahead, and wave 0 sums
-// the four partial products through LDS.  After that lane l of wave 0 holds, for token l % 32, the logits of experts
-// 32 nb + 8 (q / 4) + 4 (l / 32) + q % 4 (q = 0..15); lane l ^ 32 holds the
-// token's other half.  Top-k: k rounds, each lane proposes its largest
-// unselected logit (equal: lower id), the two halves compare over one
-// shuffle, the owner marks the winner.
-template <typename T, int NB>
+// operands loaded straight into registers D - 1 blocks ahead, and wave 0 sums
+// the four partial products through LDS.  After that lane l of wave 0 holds,
+// for token l % 32, the logits of experts 32 nb + 8 (q / 4) + 4 (l / 32) + q % 4
+// (q = 0..15); lane l ^ 32 holds the token's other half.  Top-k: k rounds, each
+// lane proposes its largest unselected logit (equal: lower id), the two halves
+// compare over one shuffle, the owner marks the winner.
+template <typename T, int NB, int D>
 __global__ __launch_bounds__(64 * kRouterWaves) void router_fwd_kernel(
     const T* __restrict__ X, const T* __restrict__ Wr, int64_t T_, int h, int E, int k,
     int32_t* __restrict__ idx, float* __restrict__ gates, float* __restrict__ logits) {
@@ -78,10 +78,8 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_fwd_kernel(
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[nb][q] = 0.f;
   // this wave's K blocks: w, w + W, w + 2W, ...; the operands of the next
-  // D - 1 blocks are in flight (at 4096 tokens, h 2048, 64 logits a wave has 8
-  // blocks to go through: three ahead 29 us, one ahead 33; with 32 logits or
-  // fewer one ahead is as fast)
-  constexpr int W = kRouterWaves, D = NB == 2 ? 4 : 2;
+  // D - 1 blocks are in flight
+  constexpr int W = kRouterWaves;
   typename K::Raw a[D], b[D][NB];
   const int nkb = h / K::KB;
   auto fetch = [&](int d, int kb) {
@@ -559,16 +557,23 @@ __global__ __launch_bounds__(256) void router_reduce_kernel(const float* __restr
 }  // namespace
 
 hipError_t launch_router_fwd(int dtype, const void* X, const void* Wr, int64_t T, int h, int E,
-                             int k, int32_t* idx, float* gates, float* logits, hipStream_t s) {
+                             int k, int32_t* idx, float* gates, float* logits, int cus,
+                             hipStream_t s) {
   if (T == 0) return hipSuccess;
   const int blocks = (int)((T + 31) / 32);
   const dim3 grid(blocks), block(64 * kRouterWaves);
   if (dtype == 0) {
     const bf16_t *x = (const bf16_t*)X, *wr = (const bf16_t*)Wr;
     if (E <= 32)
-      router_fwd_kernel<bf16_t, 1><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
+      router_fwd_kernel<bf16_t, 1, 2><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
+    else if (E <= 64 && blocks <= cus)
+      // one workgroup per CU: three K blocks in flight take 270 registers (one wave
+      // per SIMD) and shorten the chain of loads (4096 tokens, h 2048, 64 logits:
+      // 29 us, one block ahead 33); with more workgroups several waves per SIMD
+      // hide it better (16384 tokens: 66 us against 46, 65536: 261 against 134)
+      router_fwd_kernel<bf16_t, 2, 4><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
     else if (E <= 64)
-      router_fwd_kernel<bf16_t, 2><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
+      router_fwd_kernel<bf16_t, 2, 2><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
     else if (E <= 128)
       router_fwd_wide_kernel<bf16_t, 1><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
     else
@@ -576,9 +581,9 @@ hipError_t launch_router_fwd(int dtype, const void* X, const void* Wr, int64_t T
   } else {
     const float *x = (const float*)X, *wr = (const float*)Wr;
     if (E <= 32)
-      router_fwd_kernel<float, 1><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
+      router_fwd_kernel<float, 1, 2><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
     else if (E <= 64)
-      router_fwd_kernel<float, 2><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
+      router_fwd_kernel<float, 2, 2><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
     else if (E <= 128)
       router_fwd_wide_kernel<float, 1><<<grid, block, 0, s>>>(x, wr, T, h, E, k, idx, gates, logits);
     else

@@ -257,6 +257,27 @@ def test_router_tile_rules(mf, T, E, k):
     assert relerr(host(dWr), R["dWr"]) <= TOL["bf16"]
 
 
+# Narrow routers on both sides of one workgroup of 32 tokens per CU, where the
+# operands' depth in flight changes: the same sums.
+@pytest.mark.parametrize("E,h", [(33, 64), (64, 448)])
+def test_router_narrow_depth(mf, E, h):
+    t = torch()
+    T = 32 * t.cuda.get_device_properties(0).multi_processor_count
+    log(f"router narrow depth E={E} h={h}")
+    gen = t.Generator(device="cuda")
+    gen.manual_seed(E)
+    X = t.randn((T + 1, h), generator=gen, device="cuda").bfloat16()
+    Wr = (t.randn((E, h), generator=gen, device="cuda") / 8).bfloat16()
+    out = []
+    for n in (T, T + 1):
+        idx, gates = t.empty((n, 4), dtype=t.int32, device="cuda"), t.empty((n, 4), device="cuda")
+        logits = t.empty((n, E), device="cuda")
+        mf.memfine_router_fwd(mf.make_shape(n, h, 64, E, 4, mf.BF16), X[:n], Wr, idx, gates, logits)
+        assert relerr(host(logits), (X[:n].double() @ Wr.double().T).cpu().numpy()) <= 1e-5
+        out.append((idx[:T], gates[:T], logits[:T]))
+    assert all(t.equal(a, b) for a, b in zip(*out))
+
+
 # The top-k of wide routers on logits that tie (+0 and -0 among them), are
 # infinite, or are not numbers (never selected): X is one-hot, so a token's
 # logits are a column of Wr.
