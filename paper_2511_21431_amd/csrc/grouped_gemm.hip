@@ -2353,12 +2353,15 @@ constexpr int kThinRows = 48, kThinRowsWalked = 16, kBigRows = 160;
 constexpr int kFull = 85;  // percent of the CUs
 enum RowTile { kThinTile, kSmallTile, kBigTile };
 inline int64_t rows_per_group(const GemmArgs& g) { return ((int64_t)g.n + g.groups - 1) / g.groups; }
-template <class P> RowTile row_tile(const GemmArgs& g) {  // P: a problem on 256 x 256 tiles
-  const int64_t rows = rows_per_group(g);
+// 256 x 256 tiles of average experts, with a quarter tile more in each for uneven
+// loads.  P: a problem on such tiles
+template <class P> int64_t big_tiles(const GemmArgs& g) {
+  const int64_t mt4 = std::max<int64_t>(4, (rows_per_group(g) + 63) / 64 + 1);
+  return g.groups * mt4 * ((P::ncols(g) + P::BNU - 1) / P::BNU) / 4;
+}
+template <class P> RowTile row_tile(const GemmArgs& g) {
+  const int64_t rows = rows_per_group(g), tiles = big_tiles<P>(g);
   if (rows <= (g.E <= 64 ? kThinRows : kThinRowsWalked)) return kThinTile;
-  // m-tiles of an average expert in quarters, with a quarter more for uneven loads
-  const int64_t mt4 = std::max<int64_t>(4, (rows + 63) / 64 + 1);
-  const int64_t tiles = g.groups * mt4 * ((P::ncols(g) + P::BNU - 1) / P::BNU) / 4;
   const int64_t rounds = (tiles + g.cus - 1) / g.cus;
   if (100 * tiles >= kFull * rounds * g.cus) return kBigTile;
   return rows >= kBigRows && 2 * tiles > g.cus ? kBigTile : kSmallTile;
@@ -2393,7 +2396,9 @@ template <class P> bool wgrad_big(const GemmArgs& g) {  // P: a problem on 256 x
 // 512 that are resident): 36 m-tiles x 8 (FC1 dgrad at 4096 slots, h 1024, F
 // 1408) left half the CUs with twice the others' work, 336 -> 256 us, and
 // 36 x 22 (FC1) 274 -> 237 us; past it the larger tile's operand reuse wins
-// (16384 slots, F 2048: 1103 against 1162 us for FC1).
+// (16384 slots, F 2048: 1103 against 1162 us for FC1).  Below it the larger tile
+// leads only where its grid fills the 512 exactly and all loads are equal (512 or
+// 1024 tiles: by 2 to 8 %; Dirichlet(2) loads on the same shapes: 10 to 60 % slower).
 constexpr int kF32SmallGrid = 1280;
 //
 // Every problem takes direct copies into LDS: the dgrads (an activation-row
@@ -2449,15 +2454,25 @@ hipError_t launch_pair(const GemmArgs& g_in, hipStream_t s) {
 
 // The three products that read what the recomputation wrote, as one launch
 // where each alone takes the small tiles because it would leave CUs idle: one
-// launch's last round and latency instead of three.
+// launch's last round and latency instead of three.  Measured, the whole
+// backward against separate launches, balanced / Dirichlet(2) loads.  bf16: 16
+// experts, h = F = 512: 0.86 / 0.85 at 16 rows per expert, 0.88 / 0.83 at 160, 0.93 / 0.82
+// at 300; 16, 1024, 1024: 0.83 / 0.84 at 16, 0.92 / 0.88 at 160; 2, 4096, 2048:
+// 0.84 / 0.82 at 300.  Many experts (64, 512, 512: 0.95 / 0.94 at 64 rows, 1.00 / 0.97
+// at 120, 1.11 / 1.00 at 160; 128, 256, 512: 0.95 / 0.94 at 64, 1.01 / 1.01
+// at 160) give each product rounds enough of its own: from kBigRows rows only
+// while the FC1 dgrad's 256 x 256 tiles would leave over half of the CUs idle.  fp32: 0.84 to 0.90 at 16 rows, 0.98 to 1.00 at 1000, and with small grids for
+// longer (8, 256, 256: 0.91 at 4096), at worst 1.05.
 constexpr int kMergeRows = 320;
 bool bwd_merges(const GemmArgs& g) {
   if (g.tile_override != MEMFINE_TILE_AUTO) return false;
   if (g.dtype != 0)
     return ProbFC1Dgrad<float, Small>::grid(g) < kF32SmallGrid &&
            FC1W<float, Small>::grid(g) < kF32SmallGrid && FC2W<float, Small>::grid(g) < kF32SmallGrid;
-  return rows_per_group(g) < kMergeRows &&
-         row_tile<ProbFC1Dgrad<float, Big8>>(g) != kBigTile &&
+  typedef ProbFC1Dgrad<float, Big8> Dgrad;
+  const int64_t rows = rows_per_group(g);
+  return rows < kMergeRows && (rows < kBigRows || 2 * big_tiles<Dgrad>(g) < g.cus) &&
+         row_tile<Dgrad>(g) != kBigTile &&
          !wgrad_big<FC1W<float, Big8>>(g) && !wgrad_big<FC2W<float, Big8>>(g);
 }
 hipError_t launch_bwd_merged(const GemmArgs& g_in, hipStream_t s) {

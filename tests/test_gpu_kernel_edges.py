@@ -202,9 +202,10 @@ def test_dispatch_and_count_lines(mf, T, k, E, hot):
 
 
 # FC1 dgrad and both weight gradients in one launch for small problems: the
-# line of each of its conditions (rows per expert 320, fp32 grids), the bits
+# line of each of its conditions (rows per expert 320, 160 with many experts, fp32 grids), the bits
 # of the separate launches (forced by a tile option in bf16), both chunk orders.
 @pytest.mark.parametrize("T,E,h,F,dtype", [(639, 4, 192, 320, "bf16"), (640, 4, 192, 320, "bf16"),
+                                           (6360, 80, 320, 64, "bf16"), (6400, 80, 320, 64, "bf16"),
                                            (50, 5, 64, 64, "bf16"), (300, 3, 192, 128, "f32"),
                                            (200, 70, 64, 64, "f32")])
 def test_bwd_in_one_launch(mf, T, E, h, F, dtype):
