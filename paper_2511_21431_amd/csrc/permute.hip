@@ -192,7 +192,9 @@ __device__ int32_t block_exclusive_scan(int32_t* v, int m, int32_t* part) {
 // eight of a lane's loads are in flight (a thread per count, with a division to
 // find its expert and an LDS add that 64 lanes sent to one address: 24576 slots,
 // 64 experts 17.8 us, now 9.3; 6000 slots, 64 experts 9.6, now 6.5; 16384 slots,
-// 16 experts 7.4, now 6.0).
+// 16 experts 7.4, now 6.0).  Past 64 experts a thread compares one expert with all:
+// every lane then reads the same counts, several in one LDS access (shared by four
+// lanes: 2000 slots, 256 experts 22 us against 16; 1024 experts 275 against 125).
 enum RowsFrom { kScanned, kCounts, kSlots };
 template <int kFrom>
 __global__ __launch_bounds__(256) void scatter_kernel(
@@ -212,7 +214,8 @@ __global__ __launch_bounds__(256) void scatter_kernel(
     int32_t* pre = wc + E;       // [E] the expert's slots in the workgroups before this one
     int32_t* cnt = wc + 2 * E;   // [E] the counts, kept for the order
     __shared__ int32_t spart[256];
-    int lanes = 4;  // of one wave: a power of two, as many as 256 threads have per expert
+    // lanes of one wave per expert: a power of two, as many as 256 threads have for each
+    int lanes = E > 64 && nb < 4 ? 1 : 4;
     while (lanes < 64 && 2 * lanes * E <= 256) lanes *= 2;
     const int e0 = tid / lanes, es = 256 / lanes, l0 = tid & (lanes - 1);
     if constexpr (kFrom == kSlots) {
@@ -253,17 +256,28 @@ __global__ __launch_bounds__(256) void scatter_kernel(
     const int32_t total = block_exclusive_scan(tot, E, spart);
     for (int e = tid; e < E; e += 256) run[e] = tot[e] + pre[e];
     if (blockIdx.x == 0) {
-      for (int e = e0; e < E; e += es) {
-        // order: experts by descending count, ties by id
-        const int32_t c = cnt[e];
-        int rank = 0;
+      // order: experts by descending count, ties by id
+      if (E <= 64) {
+        for (int e = e0; e < E; e += es) {
+          const int32_t c = cnt[e];
+          int rank = 0;
 #pragma unroll 8
-        for (int e2 = l0; e2 < E; e2 += lanes) {
-          const int32_t c2 = cnt[e2];
-          rank += (c2 > c) || (c2 == c && e2 < e);
+          for (int e2 = l0; e2 < E; e2 += lanes) {
+            const int32_t c2 = cnt[e2];
+            rank += (c2 > c) || (c2 == c && e2 < e);
+          }
+          for (int o = 1; o < lanes; o <<= 1) rank += __shfl_xor(rank, o);
+          if (l0 == 0) {
+            counts[e] = c;
+            offsets[e] = tot[e];
+            order[rank] = e;
+          }
         }
-        for (int o = 1; o < lanes; o <<= 1) rank += __shfl_xor(rank, o);
-        if (l0 == 0) {
+      } else {
+        for (int e = tid; e < E; e += 256) {
+          const int32_t c = cnt[e];
+          int rank = 0;
+          for (int e2 = 0; e2 < E; ++e2) rank += (cnt[e2] > c) || (cnt[e2] == c && e2 < e);
           counts[e] = c;
           offsets[e] = tot[e];
           order[rank] = e;
