@@ -50,11 +50,14 @@ def _check_bwd(mf, w, seed, C, accumulate, **opts):
 
 # Weight-gradient epilogue: a 32 x 32 block is stored whole or not at all, so
 # every count of valid 64-row and 64-column pieces in a last tile of 256 or
-# 128, with dW overwritten, added to by a second chunk and added to throughout;
-# E = 80 fills the grid of the persistent launch with its quarter tiles.
+# 128, with dW overwritten, added to by a second chunk and added to throughout.
+# bf16, 160 experts of 320 x 320: 960 and 640 tiles of 256 x 256, the persistent launch
+# with its tile counter, FC2's last half round in quarter tiles; fp32 there: 2400 and
+# 1440 tiles of 128 x 128 (the smaller cases take 64 x 64).
 @pytest.mark.parametrize("h,F,E,dtype", [
     (64, 64, 4, "bf16"), (128, 192, 3, "bf16"), (192, 64, 5, "bf16"), (320, 192, 80, "bf16"),
-    (448, 320, 2, "bf16"), (192, 320, 3, "f32"), (64, 64, 2, "f32")])
+    (448, 320, 2, "bf16"), (320, 320, 160, "bf16"), (192, 320, 3, "f32"), (64, 64, 2, "f32"),
+    (320, 320, 160, "f32")])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_wgrad_tile_edges(mf, h, F, E, dtype, accumulate):
     w = mw.Workload("edge", T=321, h=h, F=F, E=E, k=2, dtype=dtype, routing="dirichlet")
@@ -149,11 +152,13 @@ def test_wgrad_tile_shape_by_rows(mf, T, E, h, F):
 
 
 # fp32: 64-row tiles below 1280 tiles of 128 x 128, the larger ones from there
-# (FC1: F / 64 = 256 column tiles x 4 and x 5 row tiles).
-@pytest.mark.parametrize("T", [512, 640])
-def test_f32_tile_shape_by_grid(mf, T):
-    w = mw.Workload("grid", T=T, h=64, F=16384, E=1, k=1, dtype="f32", routing="dirichlet")
-    log(f"f32 tile shape T={T}")
+# (FC1: F / 64 = 256 column tiles x 4 and x 5 row tiles; FC2 dgrad: 319 and 320 x 4;
+# FC2 and FC1 dgrad the same).
+@pytest.mark.parametrize("T,h,F", [(512, 64, 16384), (640, 64, 16384), (512, 64, 40832),
+                                   (512, 64, 40960), (512, 40832, 64), (512, 40960, 64)])
+def test_f32_tile_shape_by_grid(mf, T, h, F):
+    w = mw.Workload("grid", T=T, h=h, F=F, E=1, k=1, dtype="f32", routing="dirichlet")
+    log(f"f32 tile shape T={T} h={h} F={F}")
     case = mw.make_case(w, 40 + T)
     dev = device_case(w, case)
     Y = host(run_fwd(w, dev, 1))
@@ -316,10 +321,14 @@ def test_router_topk_special_logits(mf, E):
 
 
 # Router dX with the rows in registers (from 8192 tokens): a last row block of 1,
-# 244 and 255 rows, half a column block, a result larger than the cache, every reduction length, adding to dX;
-# the bits of the grouped GEMM (forced by a tile option).
+# 244 and 255 rows, half a column block, a result larger than the cache, every
+# reduction length, adding to dX; at h = 4160 a workgroup walks four or more column
+# blocks through its two LDS stages (all 33 at 33000 tokens, where the stores are
+# streamed); the bits of the grouped GEMM (forced by a tile option).
 @pytest.mark.parametrize("T,E,h", [(8191, 256, 64), (8192, 64, 64), (8193, 128, 192),
-                                   (8436, 192, 320), (8447, 256, 448), (300001, 64, 512)])
+                                   (8436, 192, 320), (8447, 256, 448), (300001, 64, 512),
+                                   (8193, 64, 4160), (8193, 128, 4160), (8193, 192, 4160),
+                                   (8193, 256, 4160), (33000, 64, 4160)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_router_dx_rows(mf, T, E, h, accumulate):
     t = torch()

@@ -1,8 +1,8 @@
 """Every GEMM launch configuration computes the same numbers.
 
 Each output element of every grouped GEMM is one thread's fp32 sum over K in
-increasing K order (MFMA steps of 16 or 2), whatever the tile shape, the tile
-order over the chip (XCD blocks, row-major), the persistent or one-tile-per-
+one fixed order (bf16: MFMA steps of 16; fp32: steps of 8, values s and 4 + s of a
+step together), whatever the tile shape, the tile order over the chip (XCD blocks, row-major), the persistent or one-tile-per-
 workgroup launch, the quarter-tile tail, the paired dgrad/wgrad launch or
 the side-stream schedule.  So all of them must give bit-identical outputs
 and gradients; the default configuration is checked against the oracle in
@@ -21,6 +21,9 @@ pytestmark = pytest.mark.gpu
 # (FC1: 64 m-tiles x 8 n-tiles at C = 1), ragged per expert
 W_BIG = mw.scaled(mw.WORKLOADS[2], T=4096, h=512, F=1024, E=8)
 W_F32 = mw.WORKLOADS[1]
+# 960 and 640 weight-gradient tiles of 256 x 256, ragged in both directions: the
+# persistent launches with a tile counter, FC2's last half round as quarter tiles
+W_WGRAD = mw.scaled(mw.WORKLOADS[2], T=700, h=320, F=320, E=160)
 
 # memfine_set_launch_options keyword arguments
 CONFIGS = ([{"raster": r} for r in range(5)]
@@ -77,7 +80,24 @@ def test_bitwise_across_launch_configs(mf, cfg, C):
         assert np.array_equal(got[key], ref[key]), (cfg, C, key)
 
 
-@pytest.mark.parametrize("cfg", [{"raster": 3}, {"split_tail": False}, {"streams": True}], ids=_ids)
+@pytest.mark.parametrize("C", [1, 3])
+@pytest.mark.parametrize("cfg", [{"raster": 1}, {"raster": 3}, {"split_tail": False},
+                                 {"streams": True}, {"streams": True, "raster": 4},
+                                 {"pair": True}, {"tile": 1}, {"tile": 2}], ids=_ids)
+def test_bitwise_across_wgrad_launches(mf, cfg, C):
+    dev, ref = _reference(W_WGRAD, 17, C)
+    log(f"wgrad launches {cfg} C={C}")
+    try:
+        mf.memfine_set_launch_options(**cfg)
+        got = _run(W_WGRAD, dev, C)
+    finally:
+        mf.memfine_set_launch_options()
+    for key in ref:
+        assert np.array_equal(got[key], ref[key]), (cfg, C, key)
+
+
+@pytest.mark.parametrize("cfg", [{"raster": 3}, {"split_tail": False}, {"streams": True},
+                                 {"pair": True}], ids=_ids)
 def test_bitwise_across_launch_configs_f32(mf, cfg):
     dev, ref = _reference(W_F32, 5, 2)
     log(f"launch config f32 {cfg}")
