@@ -22,7 +22,7 @@ SOURCES = ["api.hip", "permute.hip", "combine.hip", "grouped_gemm.hip", "mact.hi
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-    "-Wall", "-Wno-unused-function",
+    "-Wall",
     # packed fp32 VALU ops stay off: ordinary float code only
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]

@@ -1258,8 +1258,8 @@ int memfine_router_bwd(const memfine_shape* shape, const void* d_X, const void* 
   const int64_t want = std::max(1, 256 / ntn), most = std::max<int64_t>(1, T / 256);
   const int splits = (int)std::max<int64_t>(1, std::min(want, most));
   // dX (+)= dz Wr: per token in the dz kernel, or (E % 64 == 0, so that the
-  // dense dz rows are whole K tiles) as a grouped GEMM from D, which reads
-  // Wr once per 256-token tile instead of k rows of it per token
+  // dense dz rows are whole K tiles) as a product from D, which reads Wr once
+  // per block of 64 to 256 tokens instead of k rows of it per token
   const bool gemm_dx = S.E % 64 == 0;
   const int64_t o_meta = align256(T * EP * es);
   const int64_t o_order = o_meta + align256((splits + 1) * 4);

@@ -581,7 +581,7 @@ struct Tile {
   int n0;     // first output column (FC1: first f)
   int K;      // reduction length
   int r0;     // wgrad: first chunk row of the expert
-  int acc;    // wgrad: the accumulators start from the stored dW (add into it)
+  int acc;    // wgrad: the tile is added to the stored dW (by the epilogue)
 };
 
 // m-tile bound for the row-grouped grid: sum_e ceil(c_e / BM) <= this.
@@ -848,10 +848,6 @@ template <typename T, class C, bool kBwd> struct ProbFC1 {
       return f < g.F ? (uint32_t)wrow * rowb : kOOB;
     }, wave, lane);
   }
-  __device__ __forceinline__ void init_acc(const GemmArgs&, const Tile&, Accum<C>& acc, int, int,
-                                          int) const {
-    zero_acc(acc);
-  }
   __device__ __forceinline__ void commit(char* As, char* Bs, int wave, int lane) const {
     A.commit(As, wave, lane);
     B.commit(Bs, wave, lane);
@@ -1023,10 +1019,6 @@ template <typename T, class C> struct ProbFC2 {
     B.rs = make_rsrc(cptr<T>(g.W2, (int64_t)t.e * g.h * g.F), (int64_t)g.h * rowb);
     B.init([&](int r) { return t.n0 + r < g.h ? (uint32_t)(t.n0 + r) * rowb : kOOB; }, wave, lane);
   }
-  __device__ __forceinline__ void init_acc(const GemmArgs&, const Tile&, Accum<C>& acc, int, int,
-                                          int) const {
-    zero_acc(acc);
-  }
   __device__ __forceinline__ void commit(char* As, char* Bs, int wave, int lane) const {
     A.commit(As, wave, lane);
     B.commit(Bs, wave, lane);
@@ -1098,10 +1090,6 @@ template <typename T, class C> struct ProbFC2Dgrad {
       B.voff[i] = col < g.F ? (uint32_t)OB::k_of(i, wave, lane) * ld + col * sizeof(T) : kOOB;
     }
     b_ktile = ld * OB::BKE;
-  }
-  __device__ __forceinline__ void init_acc(const GemmArgs&, const Tile&, Accum<C>& acc, int, int,
-                                          int) const {
-    zero_acc(acc);
   }
   __device__ __forceinline__ void commit(char* As, char* Bs, int wave, int lane) const {
     A.commit(As, wave, lane);
@@ -1254,10 +1242,6 @@ template <typename T, class C> struct ProbFC1Dgrad {
       B.voff[i] = col < g.h ? (uint32_t)OB::k_of(i, wave, lane) * ld + col * sizeof(T) : kOOB;
     }
     b_ktile = ld * OB::BKE;
-  }
-  __device__ __forceinline__ void init_acc(const GemmArgs&, const Tile&, Accum<C>& acc, int, int,
-                                          int) const {
-    zero_acc(acc);
   }
   __device__ __forceinline__ void commit(char* As, char* Bs, int wave, int lane) const {
     A.commit(As, wave, lane);
@@ -1439,12 +1423,6 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
     }
 #pragma clang loop unroll(full)
     for (int d = 0; d < D; ++d) load_tokens(d, wave, lane, tok[d]);
-  }
-  // Adding into dW: the accumulators start at zero and the epilogue adds the
-  // old values (dW = old + this launch's sum).
-  __device__ __forceinline__ void init_acc(const GemmArgs&, const Tile&, Accum<C>& acc, int, int,
-                                          int) const {
-    zero_acc(acc);
   }
   __device__ __forceinline__ void commit(char* As, char* Bs, int wave, int lane) const {
     A.commit(As, wave, lane);
@@ -1673,7 +1651,7 @@ __device__ __forceinline__ void run_located(const GemmArgs& g, char* smem, P& p,
   const bool active = p.active(g, t, wm, wn);
   if (!prefetched) p.init(g, t, w, lane);
   Accum<C> acc;
-  p.init_acc(g, t, acc, wm, wn, lane);
+  zero_acc<C>(acc);
   constexpr int kCopies = P::OA::I + P::OB::I;  // copy instructions per wave per K tile
   const int nk = k_tiles<T, C>(t);
   if constexpr (C::DIRECT) {
@@ -2056,12 +2034,6 @@ hipError_t launch_pair_cfg(const GemmArgs& g, hipStream_t s) {
         <<<n1 + n2, C::kThreads, 0, s>>>(g, n1, n2);
   }
   return hipGetLastError();
-}
-
-// Workgroup-rounds a grid of `tiles` tiles takes on the whole chip.
-inline double rounds(int tiles, int per_cu) {
-  const int slots = 256 * per_cu;
-  return (double)((tiles + slots - 1) / slots);
 }
 
 using Big8 = Cfg<256, 256, 2, 4, 2>;        // 8 waves of 128 x 64

@@ -21,7 +21,7 @@ constexpr int kRouterWaves = 4;   // one 32-token block per workgroup, K split o
 // and step s takes its s-th element (K 2 split as 1 + 1).
 template <typename T> struct RK;
 template <> struct RK<bf16_t> {
-  static constexpr int KB = 64, STEPS = 4;
+  static constexpr int KB = 64;
   typedef u32x4_t Raw[4];
   __device__ __forceinline__ static void load(const bf16_t* row, int kb, int hh, Raw& r) {
     const u32x4_t* p = (const u32x4_t*)(row + kb * KB + 32 * hh);
@@ -36,7 +36,7 @@ template <> struct RK<bf16_t> {
   }
 };
 template <> struct RK<float> {
-  static constexpr int KB = 32, STEPS = 16;
+  static constexpr int KB = 32;
   typedef f32x4_t Raw[4];
   __device__ __forceinline__ static void load(const float* row, int kb, int hh, Raw& r) {
     const f32x4_t* p = (const f32x4_t*)(row + kb * KB + 16 * hh);
