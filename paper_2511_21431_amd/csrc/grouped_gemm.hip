@@ -2377,16 +2377,28 @@ constexpr int kF32SmallGrid = 1280;
 // operand and a K-strided weight operand) and the router's dX measured 2-8 %
 // faster with them than with register-staged copies, which remain a launch
 // option (MEMFINE_TILE_256_REG).
+//
+// Whatever the options say, 64-row tiles where 256 rows of an operand or of the output
+// would pass a buffer resource's 2^31 bytes (F or h from about 2 million; 64 of
+// at most 2^25 bytes do not, by the shape check).
+template <class P> bool wide_rows(const GemmArgs& g) {  // P: row-grouped
+  return std::max(P::ncols(g), P::reduction(g)) * (g.dtype == 0 ? 2ll : 4ll) >= (1ll << 31) / 256;
+}
 template <template <typename, class> class PT>
 hipError_t launch_auto(const GemmArgs& g_in, hipStream_t s) {
   GemmArgs g = g_in;
   typedef PT<float, Big8> Any;
   if (g.raster < 0) g.raster = Any::kRaster;
+  bool wide = false;
+  if constexpr (Any::kEqualTiles) wide = wide_rows<Any>(g);
   if (g.dtype != 0) {
     typedef std::conditional_t<PairedColumns<Any>::value, F32P, F32N> SmallF32;
-    if (PT<float, Small>::grid(g) < kF32SmallGrid) return launch_tiles<float, PT, SmallF32>(g, s);
+    if (wide || PT<float, Small>::grid(g) < kF32SmallGrid)
+      return launch_tiles<float, PT, SmallF32>(g, s);
     return launch_tiles<float, PT, Small>(g, s);
   }
+  if constexpr (Any::kEqualTiles)
+    if (wide) return launch_walk<bf16_t, PT, Thin>(g, s);
   switch (g.tile_override) {  // memfine_launch_options.tile
     case 1: return launch_tiles<bf16_t, PT, Small>(g, s);
     case 2: return launch_tiles<bf16_t, PT, Big8>(g, s);
@@ -2437,7 +2449,7 @@ hipError_t launch_pair(const GemmArgs& g_in, hipStream_t s) {
 // longer (8, 256, 256: 0.91 at 4096), at worst 1.05.
 constexpr int kMergeRows = 320;
 bool bwd_merges(const GemmArgs& g) {
-  if (g.tile_override != MEMFINE_TILE_AUTO) return false;
+  if (g.tile_override != MEMFINE_TILE_AUTO || wide_rows<ProbFC1Dgrad<float, Big8>>(g)) return false;
   if (g.dtype != 0)
     return ProbFC1Dgrad<float, Small>::grid(g) < kF32SmallGrid &&
            FC1W<float, Small>::grid(g) < kF32SmallGrid && FC2W<float, Small>::grid(g) < kF32SmallGrid;
@@ -2495,6 +2507,10 @@ hipError_t launch_router_logits(const GemmArgs& g, hipStream_t s) {
   return launch_auto<ProbLogits>(g, s);
 }
 hipError_t launch_fc1_dgrad_wgrad(const GemmArgs& g, hipStream_t s) {
+  if (wide_rows<ProbFC1Dgrad<float, Big8>>(g)) {
+    const hipError_t err = launch_fc1_dgrad(g, s);
+    return err == hipSuccess ? launch_fc1_wgrad(g, s) : err;
+  }
   return launch_pair<ProbFC1Dgrad, FC1W>(g, s);
 }
 

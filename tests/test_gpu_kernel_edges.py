@@ -416,15 +416,16 @@ def test_router_rows_past_32_bit_offsets(mf, T, dtype, accumulate):
     assert relerr(host(dWr), ref.cpu().numpy()) <= TOL[dtype]
 
 
-# Weight gradients of an expert whose tile of 256 rows spans more than 2^31
-# bytes (dW1: 256 rows of 2228224) or would if all of its rows were there (dW2: 64),
-# against float64 on the GPU.
-@pytest.mark.parametrize("h,F", [(64, 2228224), (2228224, 128)])
+# An expert whose tile of 256 rows spans more than 2^31 bytes: of dW1 (256 rows of
+# 2228224), of dW2 if all of its rows were there (64), of du (more than 240 of 300
+# rows of 4456448 bf16 values), whatever the launch options; against float64 on the GPU.
+@pytest.mark.parametrize("T,h,F,opts", [
+    (5, 64, 2228224, {}), (5, 2228224, 128, {}), (300, 64, 2228224, {}),
+    (300, 64, 2228224, {"tile": 2}), (300, 64, 2228224, {"pair": True})])
 @pytest.mark.parametrize("accumulate", [False, True])
-def test_wgrad_of_very_long_rows(mf, h, F, accumulate):
+def test_very_long_rows(mf, T, h, F, opts, accumulate):
     t = torch()
-    T = 5
-    log(f"wgrad long rows h={h} F={F} accumulate={accumulate}")
+    log(f"long rows T={T} h={h} F={F} {opts} accumulate={accumulate}")
     gen = t.Generator(device="cuda")
     gen.manual_seed(h)
 
@@ -440,8 +441,12 @@ def test_wgrad_of_very_long_rows(mf, h, F, accumulate):
     else:
         dW = [t.full(W.shape, float("nan"), device="cuda") for W in (W1, W2)]
     old = [x[0].clone() if accumulate else 0 for x in dW]
-    mf.memfine_moe_bwd(mf.make_shape(T, h, F, 1, 1, mf.BF16), 1, X, idx, gates, W1, W2, dY, dX, *dW,
-                       dg, accumulate_dW=accumulate)
+    try:
+        mf.memfine_set_launch_options(**opts)
+        mf.memfine_moe_bwd(mf.make_shape(T, h, F, 1, 1, mf.BF16), 1, X, idx, gates, W1, W2, dY, dX,
+                           *dW, dg, accumulate_dW=accumulate)
+    finally:
+        mf.memfine_set_launch_options()
     x, y, g = X.double(), dY.double(), gates.double()
     u = x @ W1[0].double().T
     gate, up = u[:, :F], u[:, F:]
