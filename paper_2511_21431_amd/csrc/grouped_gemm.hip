@@ -2309,19 +2309,24 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
 //                      32   132/152/144; 155/153/146         80/ 88/ 91; 106/ 88/ 91
 //                      64   137/157/150; 198/183/153         85/ 90/ 94; 135/117/ 94
 //                     192   332/284/175; 379/315/206        215/167/107; 246/196/140
-// With more than 64 experts a tile is found by walking them, which small
-// tiles pay more often: Thin ends at kThinRowsWalked there.
+// Between, 128 x 128 over 256 x 256, mean over ten layers where the latter give more than
+// half of the CUs a tile (equal / Dirichlet(5) / (2) / (1) loads): 0.93 / 1.04 / 0.97 /
+// 0.93 at 128 rows, 1.15 / 0.97 / 0.96 / 0.95 at 144, 1.15 / 1.01 / 0.96 / 0.91 at
+// 176, 1.11 / 1.07 / 1.02 / 1.02 at 224, 1.03 / 1.06 / 1.09 / 1.07 at 300 (a hot
+// expert's second 256-row tile starts a second round, its second 128-row tile costs
+// less; loads that are exactly equal do not occur).  So 256 x 256 from kBigRows
+// where more than half of the CUs get one (128 tiles on 256 CUs lose: 16, 1024,
+// 4096 at 320 rows FC2 118 against 71; 140 tiles win: 20, 1600, 960 at 256 rows
+// 28 against 32).
 //
-// Past Thin, 256 x 256 where their last round is nearly full (kFull; they
-// then also ride out skew, which adds small tiles first) and from kBigRows where they
-// give more than half of the CUs one (128 tiles on 256 CUs lose: 16, 1024, 4096 at 320
-// rows FC2 118 against 71; 140 tiles win: 20, 1600, 960 at 160 rows 26
-// against 30).  Over 890 points like these (five problems, seven layers, 16 to 768
-// rows) this takes 0.916 of the time of 256 x 256 tiles throughout; 8 of them are
-// slower by more than 10 %, the worst by 25 % (128, 1024, 768, FC2 dgrad at 128
-// skewed rows).  Chosen by rows alone (48 and 320): 0.940, 102 of them slower by more
-// than 10 %, forward calls by up to 1.6 times (128 experts, 160 rows).
-constexpr int kThinRows = 48, kThinRowsWalked = 16, kBigRows = 160;
+// With more than 64 experts a tile is found by walking them, which small
+// tiles pay more often: Thin ends at kThinRowsWalked, and 256 x 256 starts at
+// kBigRowsWalked, or at once where their last round is nearly full (kFull).
+//
+// Over 3090 points (five problems, 17 layers, 16 to 768 rows, up to four loads) this
+// takes 0.922 of the time of 256 x 256 tiles throughout; by rows alone (48 and
+// 320) 0.934, with forward calls of 128 experts at 160 rows at 1.6 times.
+constexpr int kThinRows = 48, kThinRowsWalked = 16, kBigRows = 200, kBigRowsWalked = 129;
 constexpr int kFull = 85;  // percent of the CUs
 enum RowTile { kThinTile, kSmallTile, kBigTile };
 inline int64_t rows_per_group(const GemmArgs& g) { return ((int64_t)g.n + g.groups - 1) / g.groups; }
@@ -2333,10 +2338,11 @@ template <class P> int64_t big_tiles(const GemmArgs& g) {
 }
 template <class P> RowTile row_tile(const GemmArgs& g) {
   const int64_t rows = rows_per_group(g), tiles = big_tiles<P>(g);
-  if (rows <= (g.E <= 64 ? kThinRows : kThinRowsWalked)) return kThinTile;
+  const bool walked = g.E > 64;
+  if (rows <= (walked ? kThinRowsWalked : kThinRows)) return kThinTile;
   const int64_t rounds = (tiles + g.cus - 1) / g.cus;
-  if (100 * tiles >= kFull * rounds * g.cus) return kBigTile;
-  return rows >= kBigRows && 2 * tiles > g.cus ? kBigTile : kSmallTile;
+  if (walked && 100 * tiles >= kFull * rounds * g.cus) return kBigTile;
+  return rows >= (walked ? kBigRowsWalked : kBigRows) && 2 * tiles > g.cus ? kBigTile : kSmallTile;
 }
 // The weight gradients (K = an expert's rows) take 256 x 256 tiles from
 // kWgradGrid (2.5 rounds of the CUs) of them.  Below, a launch lasts as long as the tiles of
@@ -2444,10 +2450,10 @@ hipError_t launch_pair(const GemmArgs& g_in, hipStream_t s) {
 // at 300; 16, 1024, 1024: 0.83 / 0.84 at 16, 0.92 / 0.88 at 160; 2, 4096, 2048:
 // 0.84 / 0.82 at 300.  Many experts (64, 512, 512: 0.95 / 0.94 at 64 rows, 1.00 / 0.97
 // at 120, 1.11 / 1.00 at 160; 128, 256, 512: 0.95 / 0.94 at 64, 1.01 / 1.01
-// at 160) give each product rounds enough of its own: from kBigRows rows only
+// at 160) give each product rounds enough of its own: from kMergeFewRows rows only
 // while the FC1 dgrad's 256 x 256 tiles would leave over half of the CUs idle.  fp32: 0.84 to 0.90 at 16 rows, 0.98 to 1.00 at 1000, and with small grids for
 // longer (8, 256, 256: 0.91 at 4096), at worst 1.05.
-constexpr int kMergeRows = 320;
+constexpr int kMergeRows = 320, kMergeFewRows = 160;
 bool bwd_merges(const GemmArgs& g) {
   if (g.tile_override != MEMFINE_TILE_AUTO || wide_rows<ProbFC1Dgrad<float, Big8>>(g)) return false;
   if (g.dtype != 0)
@@ -2455,7 +2461,7 @@ bool bwd_merges(const GemmArgs& g) {
            FC1W<float, Small>::grid(g) < kF32SmallGrid && FC2W<float, Small>::grid(g) < kF32SmallGrid;
   typedef ProbFC1Dgrad<float, Big8> Dgrad;
   const int64_t rows = rows_per_group(g);
-  return rows < kMergeRows && (rows < kBigRows || 2 * big_tiles<Dgrad>(g) < g.cus) &&
+  return rows < kMergeRows && (rows < kMergeFewRows || 2 * big_tiles<Dgrad>(g) < g.cus) &&
          row_tile<Dgrad>(g) != kBigTile &&
          !wgrad_big<FC1W<float, Big8>>(g) && !wgrad_big<FC2W<float, Big8>>(g);
 }

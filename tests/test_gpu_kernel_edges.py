@@ -93,12 +93,13 @@ def test_tile_shape_by_rows(mf, T, E, h, F):
             assert np.array_equal(other[key], B[key]), (tile, key)
 
 
-# The same with enough experts for the other lines of the rule: 16 rows per expert
-# past 64 experts, 160 rows with 160 tiles of 256 x 256 (FC2 and FC1 dgrad, 80 experts x
-# 2) and with 80 (FC1, FC2 dgrad), a nearly full last round (240 tiles, 60 rows); and
-# expert-ordered chunks, whose rows come from a few of the experts.
-@pytest.mark.parametrize("T,E,h,F", [(640, 80, 320, 64), (641, 80, 320, 64), (6360, 80, 320, 128),
-                                     (6361, 80, 320, 128), (2400, 80, 576, 64),
+# The same with enough experts for the other lines of the rule: 200 rows per expert
+# with 160 tiles of 256 x 256 (32 experts; FC2 and FC1 dgrad), past 64 experts 16 and
+# 129 rows (160 tiles; 80 for FC1 and FC2 dgrad) and a nearly full last round (240
+# tiles, 60 rows); and expert-ordered chunks, whose rows come from a few of the experts.
+@pytest.mark.parametrize("T,E,h,F", [(3184, 32, 1024, 64), (3185, 32, 1024, 64), (640, 80, 320, 64),
+                                     (641, 80, 320, 64), (5120, 80, 320, 128),
+                                     (5121, 80, 320, 128), (2400, 80, 576, 64),
                                      (2560, 32, 320, 192)])
 def test_tile_shape_by_rows_and_grid(mf, T, E, h, F):
     test_tile_shape_by_rows(mf, T, E, h, F)
