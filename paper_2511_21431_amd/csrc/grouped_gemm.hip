@@ -2364,10 +2364,14 @@ template <class P> RowTile row_tile(const GemmArgs& g) {
 //   1120 FC1 (20, 1600, 960)  1.13 1.2 1.2 1.16 1.3 1.2 1.20 1.3 1.2 1.32 1.4 .98  1.49 1.6 1.65
 constexpr int kWgradGrid = 640, kWgradRound = 448, kWgradRowsRound = 640;
 constexpr int kWgradPart = 160, kWgradRowsPart = 2048;
-template <class P> bool wgrad_big(const GemmArgs& g) {  // P: a problem on 256 x 256 tiles
-  const int64_t tiles = P::grid(g), rows = rows_per_group(g);
-  return tiles >= kWgradGrid || (tiles >= kWgradRound && rows >= kWgradRowsRound) ||
-         (tiles >= kWgradPart && rows >= kWgradRowsPart);
+// Both only where 256 x 256 tiles hang over the edges of dW little more than 128 x 128 ones
+// (8 experts, 1664 x 1344, 4316 rows: 42 against 35.75 per expert, a router,
+// forward and backward 1149 us with 128 x 128 tiles, 1191 with 256 x 256).
+template <template <typename, class> class PT> bool wgrad_big(const GemmArgs& g) {
+  const int64_t tiles = PT<float, Big8>::grid(g), rows = rows_per_group(g);
+  const bool fits = 10 * (int64_t)PT<float, Small>::grid(g) >= 9 * 4 * tiles;
+  return tiles >= kWgradGrid || (fits && tiles >= kWgradRound && rows >= kWgradRowsRound) ||
+         (fits && tiles >= kWgradPart && rows >= kWgradRowsPart);
 }
 //
 // fp32: 64-row tiles up to kF32SmallGrid 128 x 128 tiles (2.5 rounds of the
@@ -2423,7 +2427,7 @@ hipError_t launch_auto(const GemmArgs& g_in, hipStream_t s) {
     }
   } else {
     // (tile_ctr: the layer's weight gradients; the router's have equal row ranges)
-    if (g.tile_ctr != nullptr ? !wgrad_big<Any>(g) : Any::grid(g) < 128)
+    if (g.tile_ctr != nullptr ? !wgrad_big<PT>(g) : Any::grid(g) < 128)
       return launch_tiles<bf16_t, PT, Small>(g, s);
   }
   if (g.split_tail) return launch_split_cfg<PT, Big8, Quarter8>(g, s);
@@ -2463,7 +2467,7 @@ bool bwd_merges(const GemmArgs& g) {
   const int64_t rows = rows_per_group(g);
   return rows < kMergeRows && (rows < kMergeFewRows || 2 * big_tiles<Dgrad>(g) < g.cus) &&
          row_tile<Dgrad>(g) != kBigTile &&
-         !wgrad_big<FC1W<float, Big8>>(g) && !wgrad_big<FC2W<float, Big8>>(g);
+         !wgrad_big<FC1W>(g) && !wgrad_big<FC2W>(g);
 }
 hipError_t launch_bwd_merged(const GemmArgs& g_in, hipStream_t s) {
   GemmArgs g = g_in;
