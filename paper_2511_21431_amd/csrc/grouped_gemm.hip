@@ -224,8 +224,8 @@ __device__ __forceinline__ u32x2_t pack4(const float (&f)[4]) {
 // takes 8 values as 4 instructions of 2: lane half hh holds k = 4 hh .. 4 hh +
 // 3 of the step, so that instruction s multiplies k = s and 4 + s and a
 // K-contiguous operand is one 16-byte LDS read per step (one 4-byte read per
-// instruction, 32 rows on 16 banks, kept the LDS as busy as the matrix cores
-// on 32 x 32 wave tiles: FC2 at 4096 slots, h 1024, F 1408 149 -> 129 us, FC1
+// instruction, 32 rows on 16 banks, lost 60 to 75 % of the LDS's busy cycles
+// to conflicts, now none: FC2 at 4096 slots, h 1024, F 1408 149 -> 129 us, FC1
 // 237 -> 223 us).
 template <typename T> struct Mma;
 template <> struct Mma<bf16_t> {
@@ -1471,8 +1471,8 @@ template <typename T, class C, bool kFC1, int kAcc = -1> struct ProbWgrad {
   // blocks are in flight.  dW is read and written once per launch: non-temporal
   // accesses keep it from displacing the operands that other tiles and the
   // next kernels read.  (Straight from the accumulators, 16-byte accesses
-  // touch 32 rows in 32-byte pieces: four times the L2 requests, and non-
-  // temporal ones would send partial lines to memory.)  The launch is bound by
+  // touch 32 rows in 32-byte pieces: 22.9 M L2 requests per launch that writes
+  // 369 MB of dW1, now 17.1 M; and non-temporal ones would send partial lines to memory.)  The launch is bound by
   // memory where the experts have few rows: FC1 wgrad at 16384 slots, 32
   // experts, h 7168, F 2048: adding 2.36 (from the accumulators) -> 1.88 (whole
   // lines, cached) -> 1.79 ms, 3.76 GB read and written; overwriting 1.62 -> 1.43
@@ -2326,7 +2326,7 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
 // Over 3090 points (five problems, 17 layers, 16 to 768 rows, up to four loads) this
 // takes 0.922 of the time of 256 x 256 tiles throughout; by rows alone (48 and
 // 320) 0.934, with forward calls of 128 experts at 160 rows at 1.6 times.
-constexpr int kThinRows = 48, kThinRowsWalked = 16, kBigRows = 200, kBigRowsWalked = 129;
+constexpr int kThinRows = 48, kThinRowsWalked = 40, kBigRows = 200, kBigRowsWalked = 129;
 constexpr int kFull = 85;  // percent of the CUs
 enum RowTile { kThinTile, kSmallTile, kBigTile };
 inline int64_t rows_per_group(const GemmArgs& g) { return ((int64_t)g.n + g.groups - 1) / g.groups; }
@@ -2347,10 +2347,11 @@ template <class P> RowTile row_tile(const GemmArgs& g) {
 // The weight gradients (K = an expert's rows) take 256 x 256 tiles from
 // kWgradGrid (2.5 rounds of the CUs) of them.  Below, a launch lasts as long as the tiles of
 // the expert with most rows, and 128 x 128 tiles spread them over four times the
-// workgroups; but they read twice as much per product, and where the
-// rows are many and the loads even, that decides: 256 x 256 then from kWgradRound tiles
-// (1.75 rounds) with kWgradRowsRound rows per expert, and from kWgradPart tiles with
-// kWgradRowsPart rows.  Time of 128 x 128 over that of 256 x 256, overwriting
+// workgroups; but they read twice as much per product, which decides where the
+// loads are even (the host does not know).  256 x 256 below kWgradGrid only where they lead for
+// moderately uneven loads too: from kWgradPart tiles (1.75 rounds) with kWgradRows rows per
+// expert.  Elsewhere even loads pay for it (two rounds, 2048 rows: 1.3 times), and a hot
+// expert gains.  Time of 128 x 128 over that of 256 x 256, overwriting
 // dW, balanced / Dirichlet(5) / Dirichlet(1) loads:
 //   tiles (experts, h, F)         384 rows     1000 rows    2048 rows    4096 rows   16384 rows
 //    128 FC1 (8, 1024,  512)   .87 .79 .83  .93 .87 .92  .94 .89 .82  .93 .82 .87   .81 .80 .71
@@ -2362,16 +2363,14 @@ template <class P> RowTile row_tile(const GemmArgs& g) {
 //    512 FC1 (8, 1024, 2048)  1.06 1.1 .91 1.18 1.1 .98 1.33 1.1 .97 1.40 1.1 1.2  1.45 1.2 1.04
 //    560 FC2 (20, 1600, 960)   .96 1.1 .93 1.07 1.0 .77 1.13 1.0 .69 1.18 .98 .66  1.19 1.1 .92
 //   1120 FC1 (20, 1600, 960)  1.13 1.2 1.2 1.16 1.3 1.2 1.20 1.3 1.2 1.32 1.4 .98  1.49 1.6 1.65
-constexpr int kWgradGrid = 640, kWgradRound = 448, kWgradRowsRound = 640;
-constexpr int kWgradPart = 160, kWgradRowsPart = 2048;
-// Both only where 256 x 256 tiles hang over the edges of dW little more than 128 x 128 ones
-// (8 experts, 1664 x 1344, 4316 rows: 42 against 35.75 per expert, a router,
-// forward and backward 1149 us with 128 x 128 tiles, 1191 with 256 x 256).
+constexpr int kWgradGrid = 640, kWgradPart = 448, kWgradRows = 4096;
+// and only where 256 x 256 tiles hang over the edges of dW little more than 128 x 128 ones
+// (8 experts, dW of 1664 x 1344, 4316 rows: 42 against 35.75 per expert).
 template <template <typename, class> class PT> bool wgrad_big(const GemmArgs& g) {
-  const int64_t tiles = PT<float, Big8>::grid(g), rows = rows_per_group(g);
-  const bool fits = 10 * (int64_t)PT<float, Small>::grid(g) >= 9 * 4 * tiles;
-  return tiles >= kWgradGrid || (fits && tiles >= kWgradRound && rows >= kWgradRowsRound) ||
-         (fits && tiles >= kWgradPart && rows >= kWgradRowsPart);
+  const int64_t tiles = PT<float, Big8>::grid(g);
+  if (tiles >= kWgradGrid) return true;
+  return tiles >= kWgradPart && rows_per_group(g) >= kWgradRows &&
+         10 * (int64_t)PT<float, Small>::grid(g) >= 9 * 4 * tiles;
 }
 //
 // fp32: 64-row tiles up to kF32SmallGrid 128 x 128 tiles (2.5 rounds of the

@@ -94,11 +94,11 @@ def test_tile_shape_by_rows(mf, T, E, h, F):
 
 
 # The same with enough experts for the other lines of the rule: 200 rows per expert
-# with 160 tiles of 256 x 256 (32 experts; FC2 and FC1 dgrad), past 64 experts 16 and
+# with 160 tiles of 256 x 256 (32 experts; FC2 and FC1 dgrad), past 64 experts 40 and
 # 129 rows (160 tiles; 80 for FC1 and FC2 dgrad) and a nearly full last round (240
 # tiles, 60 rows); and expert-ordered chunks, whose rows come from a few of the experts.
-@pytest.mark.parametrize("T,E,h,F", [(3184, 32, 1024, 64), (3185, 32, 1024, 64), (640, 80, 320, 64),
-                                     (641, 80, 320, 64), (5120, 80, 320, 128),
+@pytest.mark.parametrize("T,E,h,F", [(3184, 32, 1024, 64), (3185, 32, 1024, 64), (1600, 80, 320, 64),
+                                     (1601, 80, 320, 64), (5120, 80, 320, 128),
                                      (5121, 80, 320, 128), (2400, 80, 576, 64),
                                      (2560, 32, 320, 192)])
 def test_tile_shape_by_rows_and_grid(mf, T, E, h, F):
@@ -118,11 +118,12 @@ def test_wgrad_tile_shape_by_grid(mf, E):
         _check_bwd(mf, w, 70 + E, 2, accumulate)
 
 
-# The rows at which fewer tiles of 256 x 256 take the larger shape: from 448 of
-# them (512 here, FC1 wgrad) 640 rows per expert, from 160 (192, FC2 wgrad of the
-# second) 2048; with a tile option forcing the other shape the bits are the same.
-@pytest.mark.parametrize("T,E,h,F", [(5119, 16, 512, 2048), (5120, 16, 512, 2048),
-                                     (2047, 2, 2048, 3072), (2048, 2, 2048, 3072)])
+# The rows at which fewer than 640 tiles of 256 x 256 take the larger shape: 4096 per
+# expert from 448 tiles (512 here, FC1 wgrad), and one that hangs over dW's edges too
+# much for it (495 tiles, dW1 of 1152 x 2112); with a tile option forcing the other shape
+# the bits are the same.
+@pytest.mark.parametrize("T,E,h,F", [(8191, 4, 2048, 2048), (8192, 4, 2048, 2048),
+                                     (22600, 11, 2112, 576)])
 def test_wgrad_tile_shape_by_rows(mf, T, E, h, F):
     w = mw.Workload("wrows", T=T, h=h, F=F, E=E, k=2, dtype="bf16", routing="dirichlet")
     log(f"wgrad tile shape T={T} E={E} h={h} F={F}")
