@@ -2506,7 +2506,10 @@ hipError_t launch_router_logits(const GemmArgs& g, hipStream_t s) {
   // the three tile heights that takes one round.  Measured at 256 logits, h
   // 7168, us for 256 x 256 / 128 x 256 / 64 x 128 tiles: 8192 tokens 106 / 112
   // / 61, 16384 112 / 117 / 104, 32768 409 / 140 / 204 (the first as quarter
-  // tiles), 65536 255 / 289 / 398, 131072 483 / 530 / 764.
+  // tiles), 65536 255 / 289 / 398, 131072 483 / 530 / 764.  Past one
+  // round of 128-row tiles the launch falls to 256-row tiles on half of the CUs, partly as
+  // quarter tiles (whole forward: 32768 tokens 178, 32769 256, 36000 214, 40000
+  // 221, 50000 245, 65536 297).
   if (g.dtype == 0 && g.tile_override == MEMFINE_TILE_AUTO) {
     GemmArgs a = g;
     if (a.raster < 0) a.raster = ProbLogits<float, Big8>::kRaster;
