@@ -2319,9 +2319,11 @@ hipError_t launch_split_cfg(const GemmArgs& g, hipStream_t s) {
 // 4096 at 320 rows FC2 118 against 71; 140 tiles win: 20, 1600, 960 at 256 rows
 // 28 against 32).
 //
-// Thin again instead of 128 x 128 where the latter would leave CUs without a tile:
+// Thin again instead of 128 x 128 where the latter would leave a quarter of the CUs
+// without a tile:
 // 8, 7168, 2048, FC2 dgrad (128 tiles) at 64 rows 70 against 99; 8, 1024, 1024, FC2
-// at 256 rows (128 tiles) 14 against 17, at 512 (256 tiles) 19 against 18; and chunks
+// at 256 rows (128 tiles) 14 against 17, at 384 (192) 18 and 18, at 512 (256) 19 against
+// 18; and chunks
 // in expert order, which hold few experts (12, 3520, 1216, 500 rows of one of
 // them: the step 1.85 ms against 2.34).
 //
@@ -2351,7 +2353,7 @@ template <class P> RowTile row_tile(const GemmArgs& g) {
   if (rows >= (walked ? kBigRowsWalked : kBigRows) && 2 * tiles > g.cus) return kBigTile;
   // (not the router's: one group without offsets)
   const int64_t small = g.groups * ((rows + 127) / 128) * ((2 * P::ncols(g) + P::BNU - 1) / P::BNU);
-  return g.offsets != nullptr && small < g.cus ? kThinTile : kSmallTile;
+  return g.offsets != nullptr && 4 * small < 3 * g.cus ? kThinTile : kSmallTile;
 }
 // The weight gradients (K = an expert's rows) take 256 x 256 tiles from
 // kWgradGrid (2.5 rounds of the CUs) of them.  Below, a launch lasts as long as the tiles of

@@ -96,10 +96,10 @@ def test_tile_shape_by_rows(mf, T, E, h, F):
 # The same with enough experts for the other lines of the rule: 200 rows per expert
 # with 160 tiles of 256 x 256 (32 experts; FC2 and FC1 dgrad), past 64 experts 40 and
 # 129 rows (160 tiles; 80 for FC1 and FC2 dgrad) and a nearly full last round (240
-# tiles, 60 rows); 256 tiles of 128 x 128 and fewer (64 x 128 then); and expert-ordered
+# tiles, 60 rows); 256 and 160 tiles of 128 x 128 (64 x 128 then); and expert-ordered
 # chunks, whose rows come from a few of the experts.
 @pytest.mark.parametrize("T,E,h,F", [(3184, 32, 1024, 64), (3185, 32, 1024, 64), (2048, 32, 1024, 64),
-                                     (2047, 32, 960, 64), (3184, 32, 128, 1024),
+                                     (2048, 32, 640, 64), (3184, 32, 128, 1024),
                                      (3185, 32, 128, 1024), (1600, 80, 320, 64),
                                      (1601, 80, 320, 64), (5120, 80, 320, 128),
                                      (5121, 80, 320, 128), (2400, 80, 576, 64),
